@@ -812,9 +812,9 @@ def bench_prefill(args, dev):
     print(json.dumps(line), flush=True)
 
 
-BUILD_PHASES = [("sketch pass", 2), ("Cholesky", 3), ("R^-1, B", 4), ("B B^T", 5),
-                ("iteration (Cholesky + R2^-1 + basis)", 6), ("last pass", 7), ("Cholesky", 8),
-                ("R^-1, B", 9), ("B B^T", 10), ("Jacobi", 11), ("V rows", 12), ("T", 13), ("U pass", 14)]
+BUILD_PHASES = [("sketch pass", 2), ("Cholesky of G, C", 3), ("M = B B^T", 4),
+                ("iteration (Cholesky of M, basis)", 5), ("last pass", 6), ("Cholesky of G, C", 7),
+                ("M = B B^T", 8), ("Cholesky of M", 9), ("Jacobi", 10), ("T", 11), ("output pass", 14)]
 
 
 def builder_phase_trace(args, bd, keys, values, H, n_tok, seg, omega, lay, cache, block_off, ws, dev):

@@ -27,6 +27,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                 "-Xarch_device", "-Wframe-larger-than=0", "-Xarch_device", "-Werror=frame-larger-than"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", f"-I{INCLUDE}", f"-I{CSRC}"]
+SVD_INSTANCES = [(2, 128), (4, 128), (2, 64), (4, 64)]      # (element bytes, head_dim)
 INSTANCES = [("BF16", 128), ("BF16", 64), ("F32", 128), ("F32", 64)]
 
 # every source the kernels are built from (the bench hashes these to tie counter
@@ -58,9 +59,14 @@ def _jobs(bdir, trace):
         obj = os.path.join(bdir, src.replace(".hip", ".o"))
         jobs.append(([HIPCC, *COMMON, f"--offload-arch={ARCH}", *DEVICE_FLAGS, "-c",
                       os.path.join(CSRC, src), "-o", obj], obj))
-    obj = os.path.join(bdir, f"sekv_build{sfx}.o")        # the builder's SVD has phase marks too
-    jobs.append(([HIPCC, *COMMON, f"--offload-arch={ARCH}", *DEVICE_FLAGS, *tflag, "-c",
+    obj = os.path.join(bdir, "sekv_build.o")
+    jobs.append(([HIPCC, *COMMON, f"--offload-arch={ARCH}", *DEVICE_FLAGS, "-c",
                   os.path.join(CSRC, "sekv_build.hip"), "-o", obj], obj))
+    for e, d in SVD_INSTANCES:                            # the builder's SVD has phase marks too
+        obj = os.path.join(bdir, f"sekv_svd_{e}_{d}{sfx}.o")
+        jobs.append(([HIPCC, *COMMON, f"--offload-arch={ARCH}", *DEVICE_FLAGS, *tflag,
+                      f"-DSEKV_ELEM={e}", f"-DSEKV_D={d}", "-c",
+                      os.path.join(CSRC, "sekv_svd_inst.hip"), "-o", obj], obj))
     obj = os.path.join(bdir, f"sekv_api{sfx}.o")
     jobs.append(([HIPCC, *COMMON, f"--offload-arch={ARCH}", *tflag, "-c",
                   os.path.join(CSRC, "sekv_api.cpp"), "-o", obj], obj))

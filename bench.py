@@ -812,8 +812,8 @@ def bench_prefill(args, dev):
     print(json.dumps(line), flush=True)
 
 
-BUILD_PHASES = [("sketch pass", 2), ("Cholesky of G, C", 3), ("M = B B^T", 4),
-                ("iteration (Cholesky of M, basis)", 5), ("last pass", 6), ("Cholesky of G, C", 7),
+BUILD_PHASES = [("sketch pass", 2), ("P P^T", 3), ("Cholesky of it", 4), ("basis", 5),
+                ("last pass", 6), ("Cholesky of G, C", 7),
                 ("M = B B^T", 8), ("Cholesky of M", 9), ("Jacobi", 10), ("T", 11), ("output pass", 14)]
 
 

@@ -6,8 +6,8 @@
 //              pivots fall below 1e-8 of the largest diagonal (a rank-deficient sketch keeps
 //              k < l columns); C = R^-T in the same loop, so Q = Y C^T is an orthonormal basis
 //              of the sketch's range and B = Q^T X = C P; M = B B^T (float64)
-//   iterate    each subspace iteration sketches again with an orthonormal basis of B's row
-//              space, C2 B with C2 the inverse factor of M (pivoted Cholesky again)
+//   iterate    each subspace iteration sketches again with an orthonormal basis of P's (and
+//              B's) row space, C_P P with C_P the inverse factor of P P^T
 //   diagonal   M = E diag(sigma^2) E^T by one-sided Jacobi on the columns of M's Cholesky
 //              factor (W W^T = M; W J has orthogonal columns E diag(sigma))
 //   output     T = C^T E; a last pass over X forms U = Y T and V diag(sigma) = X^T U
@@ -39,6 +39,7 @@ namespace sekv {
 namespace {
 
 constexpr int kMaxL = 40;                       // largest sketch width
+template <bool B> struct Bool { static constexpr bool value = B; };
 
 typedef double d4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
@@ -157,77 +158,130 @@ __device__ inline double rsqrt64(double x) {
 
 // ---------------------------------------------------------------------------
 // Cholesky with diagonal pivoting of the symmetric positive semi-definite n x n matrix in
-// g (one wave; lane i owns column i), destroyed.  Step j takes the largest remaining
-// diagonal entry p (compared at 20 bits: a near-maximum serves as well; ties to the lower
-// index) and forms row j of R by the left-looking recurrence
+// g (one wave; lane i owns column i), destroyed.  A step takes the largest remaining diagonal
+// entry p (compared at 20 bits: a near-maximum serves as well; ties to the lower index) and
+// forms row j of R, A ~ R^T R:
 //   R[j][i] = (A[p][i] - sum_{m < j} R[m][p] R[m][i]) / R[j][p].
 // It stops when the largest remaining entry is not above tau times the largest initial one;
-// returns the number of steps k.
-//   INV: g's row j becomes row j of C = R^-T over the original indices (the inverse of the
-//        factor with its columns in pivot order: A ~ R^T R, C A C^T = I).  C follows the same
-//        recurrence from the columns of the identity, and a column needs R's entries before
-//        its pivot step and C's from it on, so the two share the storage.
+// returns the number of steps k.  Row j of the result is stored at g's row p (nobody needs
+// the rows in pivot order; piv[j] = p), rows that were no pivot are zero.
+//   INV: row j of C = R^-T over the original indices (C A C^T = I on the pivots).  C follows
+//        the same recurrence from the columns of the identity, and a column needs R's entries
+//        before its pivot step and C's from it on, so the two share the storage.
 //   not INV: row j of R over the original indices.
-// Rows k and up are zero.  In storage, row j is exchanged with the pivot's row, so the rows
-// already formed are 0 .. j - 1.  About 1300 cycles a step at j = 20: the sum's LDS reads
-// and float64 FMAs, and the chain pivot -> row -> diagonal.
+// Panels of 8 steps: within one, rows are kept in registers and a step subtracts the panel's
+// terms itself (at most 7, their factors by v_readlane); after it the remaining rows of g take
+// all 8 terms by float64 MFMA.  A step is then about 55 vector instructions and one LDS round
+// trip; with every sum read back from LDS (a left-looking loop over all rows) it was 2400
+// cycles, and the four factorisations of a span side 190 of its 435 us.
 // ---------------------------------------------------------------------------
 template <int NL, int LS, bool INV>
-__device__ __forceinline__ int chol(double (*g)[LS], int n, double tau, int lane) {
-    const int li = min(lane, NL - 1);
+__device__ __forceinline__ int chol(double (*g)[LS], int *piv, int n, double tau, int lane) {
+    constexpr int NT = NL / 16;
+    const int li = min(lane, NL - 1), c16 = lane & 15, q = lane >> 4;
     double dg = lane < n ? g[li][li] : -1.0;
     bool taken = lane >= n;
-    int pos = lane, own = lane;          // storage row of original row `lane`, and back
     double floor_ = 0.0;
     int k = 0;
-    for (int j = 0; j < n; ++j) {
-        const uint32_t hi = uint32_t(uint64_t(__double_as_longlong(dg)) >> 32);
-        const bool live = !taken && dg > 0.0;
-        const uint32_t key = wave_max_u32(live ? (hi & ~63u) | uint32_t(63 - lane) : 0u);
-        const double ry = rsqrt64(live ? dg : 1.0);
-        if (__builtin_amdgcn_readfirstlane(int(key)) == 0) break;
-        const int p = 63 - (__builtin_amdgcn_readfirstlane(int(key)) & 63);
-        const double v = lane_get(dg, p);
-        if (j == 0) floor_ = tau * v;
-        if (!(v > floor_)) break;
-        const double rinv = lane_get(ry, p);
-        const int pp = __builtin_amdgcn_readlane(pos, p), o = __builtin_amdgcn_readlane(own, j);
-        const double va = g[pp][li], vj = g[j][li];
-        const double cf = lane < j ? g[li][p] : 0.0;         // R[m][p] in lane m
-        wave_sync();
-        if (lane < NL && pp != j) g[pp][li] = vj;
-        if (INV && lane < j) g[li][p] = 0.0;                 // column p holds C from here on
-        if (lane == pp) own = o;
-        if (lane == o) pos = pp;
-        if (lane == p) pos = j;
-        if (lane == j) own = p;
-        wave_sync();
-        double acc[4] = {(taken || lane == p) ? 0.0 : va, 0.0, 0.0, 0.0};
-#pragma unroll 1
-        for (int m = 0; m < j; m += 4) {
+    for (int jb = 0;; jb += 8) {
+        double w[8];
+        int pr[8];
+        bool fresh = false;                          // became a pivot in this panel
+        bool stop = false;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] = fma(-lane_get(cf, m + u), g[m + u][li], acc[u]);
+        for (int jj = 0; jj < 8; ++jj) {
+            w[jj] = 0.0;
+            pr[jj] = 0;
+            if (stop || jb + jj >= n) { stop = true; continue; }
+            const uint32_t hi = uint32_t(uint64_t(__double_as_longlong(dg)) >> 32);
+            const bool live = !taken && dg > 0.0;
+            const uint32_t key = wave_max_u32(live ? (hi & ~63u) | uint32_t(63 - lane) : 0u);
+            const double ry = rsqrt64(live ? dg : 1.0);
+            const uint32_t ku = uint32_t(__builtin_amdgcn_readfirstlane(int(key)));
+            const int p = 63 - int(ku & 63u);
+            const double v = lane_get(dg, p);
+            if (jb + jj == 0) floor_ = tau * v;
+            if (ku == 0 || !(v > floor_)) { stop = true; continue; }
+            pr[jj] = p;
+            const double va = g[p][li];
+            const double rinv = lane_get(ry, p);
+            double acc = (taken || lane == p) ? 0.0 : va;
+            if (INV && taken && !fresh) acc = va;
+#pragma unroll
+            for (int m = 0; m < jj; ++m) {
+                acc = fma(-lane_get(w[m], p), w[m], acc);
+                if (INV && lane == p) w[m] = 0.0;    // column p holds C from here on
+            }
+            double res = acc * rinv;
+            if (!INV && taken) res = 0.0;
+            if (lane == p) res = INV ? rinv : v * rinv;
+            w[jj] = res;
+            if (!taken) dg = fma(-res, res, dg);
+            if (lane == p) {
+                taken = fresh = true;
+                piv[jb + jj] = p;
+            }
+            k = jb + jj + 1;
         }
-        double res = ((acc[0] + acc[1]) + (acc[2] + acc[3])) * rinv;
-        if (!INV && taken) res = 0.0;
-        if (lane == p) res = INV ? rinv : v * rinv;
-        if (lane < NL) g[j][li] = res;
-        if (!taken) dg = fma(-res, res, dg);
-        if (lane == p) taken = true;
+        wave_sync();                                  // g's rows have been read
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj)
+            if (jb + jj < k && lane < NL) g[pr[jj]][lane] = w[jj];
         wave_sync();
-        k = j + 1;
+        // rows without a pivot take the panel's terms.  With INV, the panel's pivot columns
+        // hold C from here on: what is above their own step (older rows) becomes zero, and
+        // the rows without a pivot restart from the identity's zero
+        const uint64_t tm = __ballot(taken), fm = __ballot(fresh);
+        if (stop || jb + 8 >= n) {
+            if (INV) {
+                for (uint64_t old = tm & ~fm & ((uint64_t(1) << n) - 1); old; old &= old - 1)
+                    if (fresh) g[__builtin_ctzll(old)][lane] = 0.0;
+                wave_sync();
+            }
+            break;
+        }
+        double op[2][NT], om_[2][NT];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int row = q == 0 ? pr[4 * kk] : q == 1 ? pr[4 * kk + 1] : q == 2 ? pr[4 * kk + 2] : pr[4 * kk + 3];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                op[kk][t] = g[row][16 * t + c16];
+                om_[kk][t] = ((tm >> (16 * t + c16)) & 1) ? 0.0 : -op[kk][t];
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < NT; ++it) {
+            const uint32_t fr = uint32_t(fm >> (16 * it + q));           // bit 4 e: row q + 4 e is the panel's
+#pragma unroll
+            for (int jt = 0; jt < NT; ++jt) {
+                const bool restart = INV && ((fm >> (16 * jt + c16)) & 1);
+                d4_t s;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s[e] = g[16 * it + q + 4 * e][16 * jt + c16];
+                    if (restart && !((fr >> (4 * e)) & 1)) s[e] = 0.0;
+                }
+                s = mfma64(om_[0][it], op[0][jt], s);
+                s = mfma64(om_[1][it], op[1][jt], s);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[16 * it + q + 4 * e][16 * jt + c16] = s[e];
+            }
+        }
+        wave_sync();
     }
-    // rows past k; with INV also what columns without a pivot still hold of R
-    const int z0 = INV && !taken ? 0 : k;
-    if (lane < NL)
-        for (int m = z0; m < NL; ++m) g[m][lane] = 0.0;
-    wave_sync();
+    if (k < n) {
+        const uint64_t tm = __ballot(taken && lane < n);
+        for (int m = 0; m < NL; ++m)
+            if (lane < NL && (!((tm >> m) & 1) || (INV && !taken))) g[m][lane] = 0.0;
+        wave_sync();
+    }
     return k;
 }
 
 // ---------------------------------------------------------------------------
-// One-sided Jacobi: rotates the columns of W (W[i][m] = g[m][i], an n x n matrix, n even)
-// until they are pairwise orthogonal; then writes the normalised columns E and their
+// One-sided Jacobi: rotates the columns of W (an n x n matrix, n even)
+// until they are pairwise orthogonal (column m starts as row piv[m] of g, m < k); then writes the normalised columns E and their
 // norms in descending order: g[i][c] = E[i][c], sig[c] (both zero past column n).
 //
 // Columns sit at positions 0 .. n - 1 and every rotation also exchanges the two: rounds over
@@ -245,17 +299,18 @@ __device__ __forceinline__ int chol(double (*g)[LS], int n, double tau, int lane
 // the rotation, 28 DPP moves, about 60 for the angle.
 // ---------------------------------------------------------------------------
 template <int NL, int LS>
-__device__ __forceinline__ void jacobi_columns(double (*g)[LS], double *sig, double *nrm, int n, int sweeps, int lane) {
+__device__ __forceinline__ void jacobi_columns(double (*g)[LS], const int *piv, int k, double *sig, double *nrm,
+                                               int n, int sweeps, int lane) {
     constexpr int RW = NL > 32 ? 14 : 11;                      // rows per lane (3 RW >= largest n)
     const int np = n / 2, grp = lane / 20, s = lane % 20;
     const bool active = grp < 3 && s < np, last = s == np - 1;
+    const int pa = active && 2 * s < k ? piv[2 * s] : 0, pb = active && 2 * s + 1 < k ? piv[2 * s + 1] : 0;
     double a[RW], b[RW];
 #pragma unroll
     for (int e = 0; e < RW; ++e) {
         const int i = RW * grp + e;
-        const bool in = active && i < n;
-        a[e] = in ? g[2 * s][i] : 0.0;
-        b[e] = in ? g[2 * s + 1][i] : 0.0;
+        a[e] = active && i < n && 2 * s < k ? g[pa][i] : 0.0;
+        b[e] = active && i < n && 2 * s + 1 < k ? g[pb][i] : 0.0;
     }
     wave_sync();
     const int f0 = 4 * s, f1 = 4 * (20 + s), f2 = 4 * (40 + s);
@@ -347,7 +402,7 @@ __device__ __forceinline__ void jacobi_columns(double (*g)[LS], double *sig, dou
 // Phase marks of the diagnostic trace (builds with SEKV_PHASE_TRACE): slot 0 holds the
 // span length, then one s_memrealtime stamp per mark, for the first trace_items items.
 enum : int {
-    kSvStart = 1, kSvPass = 2, kSvChol = 3, kSvGram = 4, kSvIter = 5, kSvPass2 = 6, kSvChol2 = 7,
+    kSvStart = 1, kSvPass = 2, kSvGram = 3, kSvChol = 4, kSvIter = 5, kSvPass2 = 6, kSvChol2 = 7,
     kSvGram2 = 8, kSvCholM = 9, kSvJacobi = 10, kSvT = 11, kSvEnd = 14,
 };
 #ifdef SEKV_PHASE_TRACE
@@ -380,7 +435,11 @@ struct SvdLds {
     static constexpr int tiles = (xs > xf ? xs : xf) + XB;
     static constexpr int body = NW > 1 ? red + kAcc : kG > tiles ? kG : tiles;
     __attribute__((aligned(16))) unsigned char b[(body + 15) / 16 * 16];
-    double sig[NL], nrm[NL];
+    double sig[NL];
+    union {
+        double nrm[NL];
+        int piv[NL];
+    };
 };
 
 template <int ELEM, int D, int NT, int NW>
@@ -440,8 +499,14 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
     unsigned char *const xf_raw = NW == 1 ? sm.b + SM::xf : xs_raw;
 
     // the caller's test matrix into om (bfloat16, transposed; rows past l zero)
-    for (int c = wave; c < D; c += NW)
-        if (lane < KR) om[lane][c] = lane < l ? uint16_t(bf16_rne(a.omega[size_t(c) * a.l + lane])) : uint16_t(0);
+    for (int c0 = 16 * wave; c0 < D; c0 += 16 * NW) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = lane < l ? a.omega[size_t(c0 + u) * a.l + lane] : 0.0f;
+        if (lane < KR)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) om[lane][c0 + u] = uint16_t(bf16_rne(v[u]));
+    }
     __syncthreads();
 
     // 16 rows of X from token t on, as the A (or B) operand of a product over d: lane (c16, q)
@@ -481,9 +546,26 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
         const double v = tp[min(row, KR - 1)][min(comp, KR - 1)];
         return row < KR ? v : 0.0;
     };
+    // the upper tiles of a symmetric matrix into g, both halves, zero past l
+    auto put_sym = [&](const d4_t (&m)[NG]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0, ij = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = i; j < NT; ++j, ++ij)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int row = 16 * i + q + 4 * e, col = 16 * j + c16;
+                    const double v = row < l && col < l ? m[ij][e] : 0.0;
+                    g[row][col] = v;
+                    if (i != j) g[col][row] = v;
+                }
+        wave_sync();
+    };
     f4_t pacc[NT][DT];                  // P tiles (rows: sketch columns 16 nt + 4 q + r; column: 16 ct + c16)
-    // a pass over X with the test matrix in om: P = Y^T X into pacc, G = Y^T Y into g
-    auto sketch = [&]() __attribute__((always_inline)) {
+    // a pass over X with the test matrix in om: P = Y^T X into pacc, and with GRAM G = Y^T Y
+    // (what is returned puts it into g)
+    auto sketch = [&](auto gram_c) __attribute__((always_inline)) {
+        constexpr bool GRAM = decltype(gram_c)::value;
         phase();
         d4_t gacc[NG];
 #pragma unroll
@@ -522,7 +604,8 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
 #pragma unroll
                 for (int j = i; j < NT; ++j, ++ij)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) gacc[ij] = mfma64(double(y[i][e]), double(y[j][e]), gacc[ij]);
+                    for (int e = 0; e < 4; ++e)
+                        if constexpr (GRAM) gacc[ij] = mfma64(double(y[i][e]), double(y[j][e]), gacc[ij]);
             wave_sync();
             // P += Y^T X: contraction index (q, e) is token 4 q + e
             if constexpr (ELEM == 2) {
@@ -572,7 +655,7 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                             for (int e = 0; e < 4; ++e, at += 64) red[at] = __float_as_uint(pacc[nt][ct][e]);
                     double *rd = reinterpret_cast<double *>(red + 256 * NT * DT);
 #pragma unroll
-                    for (int i = 0; i < NG; ++i)
+                    for (int i = 0; i < (GRAM ? NG : 0); ++i)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) rd[(4 * i + e) * 64 + lane] = gacc[i][e];
                 }
@@ -587,25 +670,13 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                             for (int e = 0; e < 4; ++e, at += 64) pacc[nt][ct][e] += __uint_as_float(red[at]);
                     const double *rd = reinterpret_cast<const double *>(red + 256 * NT * DT);
 #pragma unroll
-                    for (int i = 0; i < NG; ++i)
+                    for (int i = 0; i < (GRAM ? NG : 0); ++i)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) gacc[i][e] += rd[(4 * i + e) * 64 + lane];
                 }
             }
         }
-        return [=, &g = g]() __attribute__((always_inline)) {           // G into g (both halves; zero past l)
-#pragma unroll
-            for (int i = 0, ij = 0; i < NT; ++i)
-#pragma unroll
-                for (int j = i; j < NT; ++j, ++ij)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int row = 16 * i + q + 4 * e, col = 16 * j + c16;
-                        const double v = row < l && col < l ? gacc[ij][e] : 0.0;
-                        g[row][col] = v;
-                        if (i != j) g[col][row] = v;
-                    }
-        };
+        return [=]() __attribute__((always_inline)) { put_sym(gacc); };
     };
     // C as the operand of products over its rows: cr[i][nt] = C[4 i + q][16 nt + c16]
     constexpr int K4 = KR / 4;
@@ -655,63 +726,63 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) cr[i][nt] = g[4 * i + q][16 * nt + c16];
         wave_sync();
-#pragma unroll
-        for (int i = 0, ij = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = i; j < NT; ++j, ++ij)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int row = 16 * i + q + 4 * e, col = 16 * j + c16;
-                    g[row][col] = macc[ij][e];
-                    if (i != j) g[col][row] = macc[ij][e];
-                }
-        wave_sync();
+        put_sym(macc);
     };
-    // subspace iterations: the next test matrix is an orthonormal basis of B's row space
-    // (a span of at most l tokens is spanned by its sketch already: X Omega has the rank of X for
-    // a generic Omega, and an iteration would change nothing but the rounding)
+
+    // subspace iterations: the next test matrix is an orthonormal basis of P's row space,
+    // C_P P with C_P the inverse Cholesky factor of P P^T (pivots down to the rounding of
+    // float64: P's own float32 sums bound what its small directions are worth).  P = R^T B, so
+    // this is B's row space too, without G, its factor and B; in a model of both (numpy, float32 sums,
+    // bfloat16 test matrices, spectra from flat to 10^(-i/4)) the two bases give the same error
+    // of the rank-32 factors.
+    // (A span of at most l tokens is spanned by its sketch already: X Omega has the rank of X for
+    // a generic Omega, and an iteration would change nothing but the rounding.)
     const int power = L <= l ? 0 : a.power;
     for (int it = 0; it < power; ++it) {
-        auto put_g = sketch();
+        sketch(Bool<false>{});
         __syncthreads();
         if (wave == 0) {
-            put_g();
-            wave_sync();
             SV_STAMP(kSvPass);
-            chol<NL, LS, true>(g, l, 1e-8, opaque(lane));
-            SV_STAMP(kSvChol);
-            gram_b();
-            SV_STAMP(kSvGram);
-            chol<NL, LS, true>(g, l, 1e-8, opaque(lane));
-            // C3 = C2 C (its rows 16 i.. replace those of C2, which no other tile reads), then
-            // the basis C3 P, whose operand is in registers before om takes g's place
             phase();
+            {
+                // N = P P^T (float64) from 16-column strips of P, turned in LDS
+                constexpr int SS = NL + 4;                      // strip row stride
+                d4_t nacc[NG];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                d4_t c3[NT];
+                for (int i = 0; i < NG; ++i) nacc[i] = d4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) c3[nt] = d4_t{0.0, 0.0, 0.0, 0.0};
+                for (int ct = 0; ct < DT; ++ct) {
+                    float(*const ts)[SS] = reinterpret_cast<float(*)[SS]>(sm.b + (ct & 1) * 16 * SS * 4);
 #pragma unroll
-                for (int k4 = 0; k4 < K4; ++k4) {
-                    const double c2 = g[16 * i + c16][4 * k4 + q];
+                    for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f4_t *>(&ts[c16][16 * nt + 4 * q]) = pacc[nt][ct];
+                    wave_sync();
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) c3[nt] = mfma64(c2, cr[k4][nt], c3[nt]);
+                    for (int e = 0; e < 4; ++e) {
+                        double pd[NT];
+#pragma unroll
+                        for (int lt = 0; lt < NT; ++lt) pd[lt] = double(ts[4 * e + q][16 * lt + c16]);
+#pragma unroll
+                        for (int i = 0, ij = 0; i < NT; ++i)
+#pragma unroll
+                            for (int j = i; j < NT; ++j, ++ij) nacc[ij] = mfma64(pd[i], pd[j], nacc[ij]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 wave_sync();
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) g[16 * i + q + 4 * e][16 * nt + c16] = c3[nt][e];
-                __builtin_amdgcn_sched_barrier(0);
+                put_sym(nacc);
             }
-            wave_sync();
-            double c3[NT][NT][4];
+            SV_STAMP(kSvGram);
+            chol<NL, LS, true>(g, sm.piv, l, 1e-16, opaque(lane));
+            SV_STAMP(kSvChol);
+            phase();
+            // the basis; C_P's operand is in registers before om takes g's place
+            double cp[NT][NT][4];
 #pragma unroll
             for (int lt = 0; lt < NT; ++lt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) c3[lt][nt][e] = g[16 * lt + c16][16 * nt + 4 * q + e];
+                    for (int e = 0; e < 4; ++e) cp[lt][nt][e] = g[16 * lt + c16][16 * nt + 4 * q + e];
             wave_sync();
 #pragma unroll
             for (int ct = 0; ct < DT; ++ct) {
@@ -724,7 +795,7 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
                         for (int lt = 0; lt < NT; ++lt)
-                            o[lt] = mfma64(double(pacc[nt][ct][e]), c3[lt][nt][e], o[lt]);
+                            o[lt] = mfma64(double(pacc[nt][ct][e]), cp[lt][nt][e], o[lt]);
 #pragma unroll
                 for (int lt = 0; lt < NT; ++lt) {
                     const int row = 16 * lt + c16;
@@ -740,7 +811,7 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
         __syncthreads();
     }
     // the last pass; its test matrix stays in registers for the output pass
-    auto put_g = sketch();
+    auto put_g = sketch(Bool<true>{});
     phase();
     uint4 omk[NT][NX];
 #pragma unroll
@@ -750,15 +821,14 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
     __syncthreads();
     if (wave == 0) {
         put_g();
-        wave_sync();
         SV_STAMP(kSvPass2);
-        const int k = chol<NL, LS, true>(g, l, 1e-8, opaque(lane));
+        const int k = chol<NL, LS, true>(g, sm.piv, l, 1e-8, opaque(lane));
         SV_STAMP(kSvChol2);
         gram_b();
         SV_STAMP(kSvGram2);
-        chol<NL, LS, false>(g, l, 1e-30, opaque(lane));
+        const int km = chol<NL, LS, false>(g, sm.piv, l, 1e-30, opaque(lane));
         SV_STAMP(kSvCholM);
-        jacobi_columns<NL, LS>(g, sm.sig, sm.nrm, l, a.sweeps, opaque(lane));
+        jacobi_columns<NL, LS>(g, sm.piv, km, sm.sig, sm.nrm, l, a.sweeps, opaque(lane));
         SV_STAMP(kSvJacobi);
         // components below 1e-5 of the largest singular value are numerically undetermined: zero
         if (lane < NL) {

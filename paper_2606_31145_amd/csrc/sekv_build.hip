@@ -37,14 +37,6 @@ constexpr int kSegThreads = 1024;
 constexpr int BT = 256;                 // builder threads per workgroup
 constexpr int kMaxL = 40;               // largest sketch width
 
-__device__ inline float ld_elem(const void *base, size_t i, int elem) {
-    if (elem == 2) {
-        const uint16_t u = reinterpret_cast<const uint16_t *>(base)[i];
-        return __uint_as_float(uint32_t(u) << 16);
-    }
-    return reinterpret_cast<const float *>(base)[i];
-}
-
 __device__ inline void st_elem(void *base, size_t i, float v, int elem) {
     if (elem == 2) {
         uint32_t u = __float_as_uint(v);
@@ -59,21 +51,26 @@ __device__ inline void st_elem(void *base, size_t i, float v, int elem) {
 // segmentation
 // ---------------------------------------------------------------------------
 
-// Exclusive scan of cnt[0, kSegThreads) in place (Hillis-Steele); returns the total.
-__device__ int block_scan(int *cnt, int *tmp, int tid) {
-    int v = cnt[tid];
-    for (int off = 1; off < kSegThreads; off <<= 1) {
-        tmp[tid] = v;
-        __syncthreads();
-        if (tid >= off) v += tmp[tid - off];
-        __syncthreads();
+// Exclusive prefix of each thread's v over the workgroup (kSegThreads threads); *total gets
+// the sum.  `part`: one int per wave.
+__device__ int block_scan(int v, int *part, int tid, int *total) {
+    const int lane = tid & 63, wave = tid >> 6;
+    int x = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
     }
-    tmp[tid] = v;                                       // inclusive
+    if (lane == 63) part[wave] = x;
     __syncthreads();
-    const int total = tmp[kSegThreads - 1];
-    cnt[tid] = tid > 0 ? tmp[tid - 1] : 0;
+    int base = 0, sum = 0;
+    for (int w = 0; w < kSegThreads / 64; ++w) {
+        const int p = part[w];
+        if (w < wave) base += p;
+        sum += p;
+    }
     __syncthreads();
-    return total;
+    *total = sum;
+    return base + x - v;
 }
 
 // Sum of the values in the fixed order of the segmentation rule.
@@ -89,15 +86,19 @@ __device__ double fixed_order_sum(double mine, double *part, int tid) {
     return s;
 }
 
+// One workgroup per sequence.  Bound by the latency of one CU's loads: three passes over the
+// surprisal (the two sums, whose order is fixed, and the flags), each with kAhead loads in
+// flight per thread.  Flags stay in registers as 64-token ballots, and spans and anchors come
+// from the list of flagged positions alone: 131072 tokens took 380 us with byte flags
+// in memory that each thread read back token by token.
 __global__ void __launch_bounds__(kSegThreads) segment_kernel(SegArgs a) {
+    constexpr int kAhead = 16;
     __shared__ double part[kSegThreads];
-    __shared__ int cnt[kSegThreads], tmp[kSegThreads];
-    const int tid = threadIdx.x, b = blockIdx.x;
+    __shared__ int wsum[kSegThreads / 64];
+    const int tid = threadIdx.x, b = blockIdx.x, lane = tid & 63, wave = tid >> 6;
     int n = a.n_tokens[b];
     n = n < 0 ? 0 : (n > a.N ? a.N : n);
     const float *H = a.surprisal + size_t(b) * a.N;
-    unsigned char *flag = a.ws_flag + size_t(b) * a.N;
-    unsigned char *inspan = a.ws_inspan + size_t(b) * a.N;
     int32_t *pos = a.ws_pos + size_t(b) * (a.N + 2);
     int32_t *anchor_idx = a.anchor_idx + size_t(b) * a.N;
     int32_t *span_start = a.span_start + size_t(b) * a.N;
@@ -111,71 +112,87 @@ __global__ void __launch_bounds__(kSegThreads) segment_kernel(SegArgs a) {
     {
 #pragma clang fp contract(off)
         double acc = 0.0;
-        for (int t = tid; t < n; t += kSegThreads) acc = acc + double(H[t]);
+        for (int t0 = tid; t0 < n; t0 += kAhead * kSegThreads) {
+            float h[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) h[u] = t0 + u * kSegThreads < n ? H[t0 + u * kSegThreads] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (t0 + u * kSegThreads < n) acc = acc + double(h[u]);
+        }
         const double mu = fixed_order_sum(acc, part, tid) / double(n);
         double acc2 = 0.0;
-        for (int t = tid; t < n; t += kSegThreads) {
-            const double dv = double(H[t]) - mu;
-            const double sq = dv * dv;
-            acc2 = acc2 + sq;
+        for (int t0 = tid; t0 < n; t0 += kAhead * kSegThreads) {
+            float h[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) h[u] = t0 + u * kSegThreads < n ? H[t0 + u * kSegThreads] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (t0 + u * kSegThreads < n) {
+                    const double dv = double(h[u]) - mu;
+                    const double sq = dv * dv;
+                    acc2 = acc2 + sq;
+                }
         }
         const double sigma = sqrt(fixed_order_sum(acc2, part, tid) / double(n));
         const double as = a.alpha * sigma;
         thr = mu + as;
     }
-    // 2. boundary and window flags; inspan cleared
-    for (int t = tid; t < n; t += kSegThreads) {
-        flag[t] = (double(H[t]) > thr || t >= n - a.window) ? 1 : 0;
-        inspan[t] = 0;
-    }
-    __syncthreads();
-    // 3. positions of the flagged tokens, in order, between sentinels -1 and n
-    const int chunk = (n + kSegThreads - 1) / kSegThreads;
-    const int t0 = tid * chunk, t1 = min(n, t0 + chunk);
-    int c = 0;
-    for (int t = t0; t < t1; ++t) c += flag[t];
-    cnt[tid] = c;
-    __syncthreads();
-    const int m = block_scan(cnt, tmp, tid);
-    {
-        int w = cnt[tid];
-        for (int t = t0; t < t1; ++t)
-            if (flag[t]) pos[1 + w++] = t;
+    // 2. positions of the flagged tokens (boundaries and the local window), in order, between
+    //    sentinels -1 and n.  A thread owns 64 consecutive tokens of a tile of 65536: its
+    //    wave forms the 64 ballots, one group of 64 tokens after another.
+    constexpr int kTileTokens = 64 * kSegThreads;
+    int m = 0;
+    for (int t0 = 0; t0 < n; t0 += kTileTokens) {
+        const int w0 = t0 + wave * 64 * 64;                  // the wave's first token
+        uint64_t mine = 0;
+        for (int g0 = 0; g0 < 64 && w0 + g0 * 64 < n; g0 += kAhead) {
+            float h[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int t = w0 + (g0 + u) * 64 + lane;
+                h[u] = t < n ? H[t] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int t = w0 + (g0 + u) * 64 + lane;
+                const uint64_t word = __ballot(t < n && (double(h[u]) > thr || t >= n - a.window));
+                if (lane == g0 + u) mine = word;
+            }
+        }
+        int total;
+        int at = m + block_scan(__popcll(mine), wsum, tid, &total);
+        const int first = w0 + lane * 64;
+        for (uint64_t x = mine; x; x &= x - 1) pos[1 + at++] = first + __builtin_ctzll(x);
+        m += total;
     }
     if (tid == 0) { pos[0] = -1; pos[m + 1] = n; }
     __syncthreads();
-    // 4. the m + 1 gaps between consecutive positions: long ones are spans
+    // 3. the m + 1 gaps between consecutive positions: long ones are spans; the tokens of the
+    //    others, and the position that ends each gap but the last, are anchors
     const int ng = m + 1;
     const int gchunk = (ng + kSegThreads - 1) / kSegThreads;
-    const int g0 = tid * gchunk, g1 = min(ng, g0 + gchunk);
-    c = 0;
-    for (int i = g0; i < g1; ++i) c += (pos[i + 1] - pos[i] - 1 >= a.min_span) ? 1 : 0;
-    cnt[tid] = c;
-    __syncthreads();
-    const int ns = block_scan(cnt, tmp, tid);
-    {
-        int w = cnt[tid];
-        for (int i = g0; i < g1; ++i) {
-            const int s = pos[i] + 1, L = pos[i + 1] - pos[i] - 1;
-            if (L >= a.min_span) {
-                span_start[w] = s;
-                span_len[w] = L;
-                ++w;
-                for (int t = s; t < s + L; ++t) inspan[t] = 1;
-            }
-        }
+    const int g0 = min(ng, tid * gchunk), g1 = min(ng, g0 + gchunk);
+    int cs = 0, ca = 0;
+    for (int i = g0; i < g1; ++i) {
+        const int L = pos[i + 1] - pos[i] - 1;
+        if (L >= a.min_span) ++cs;
+        else ca += L;
+        if (i < m) ++ca;
     }
-    __syncthreads();
-    // 5. anchors: every token outside the spans, in order
-    c = 0;
-    for (int t = t0; t < t1; ++t) c += inspan[t] ? 0 : 1;
-    cnt[tid] = c;
-    __syncthreads();
-    const int na = block_scan(cnt, tmp, tid);
-    {
-        int w = cnt[tid];
-        for (int t = t0; t < t1; ++t)
-            if (!inspan[t]) anchor_idx[w++] = t;
+    int ns, na;
+    int ws = block_scan(cs, wsum, tid, &ns);
+    int wa = block_scan(ca, wsum, tid, &na);
+    for (int i = g0; i < g1; ++i) {
+        const int p0 = pos[i], p1 = pos[i + 1], L = p1 - p0 - 1;
+        if (L >= a.min_span) {
+            span_start[ws] = p0 + 1;
+            span_len[ws] = L;
+            ++ws;
+        } else {
+            for (int t = p0 + 1; t < p1; ++t) anchor_idx[wa++] = t;
+        }
+        if (i < m) anchor_idx[wa++] = p1;
     }
     if (tid == 0) { a.n_anchors[b] = na; a.n_spans[b] = ns; }
 }
@@ -195,74 +212,115 @@ __device__ inline void flag_table(const BuildArgs &a) {
     __hip_atomic_fetch_or(a.error, kErrSelRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// grid = B * Hkv * rows workgroups; workgroup (pair, y) copies anchor rows
-// [64 y, 64 y + 64) and summarises span y.
-__global__ void __launch_bounds__(BT) gather_kernel(BuildArgs a, int rows) {
-    const int pair = blockIdx.x / rows, b = pair / a.Hkv, g = pair % a.Hkv;
-    const int y = blockIdx.x % rows, tid = threadIdx.x;
-    const int d = a.d, e = a.elem;
-    const size_t tok0 = size_t(pair) * a.N;                 // row of token 0 of (b, g)
+// Sixteen bytes of stored values as float32.
+template <int ELEM>
+__device__ inline void unpack16(const uint4 &v, float (&f)[16 / ELEM]) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (ELEM == 2) {
+            f[2 * i] = __uint_as_float(w[i] << 16);
+            f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+        } else {
+            f[i] = __uint_as_float(w[i]);
+        }
+    }
+}
+
+// grid = B * Hkv * (ab + M_max) workgroups: of a pair's, the first ab copy 64 anchor rows each,
+// the others summarise one span each.  Both move 16-byte pieces, a row per D ELEM / 16
+// lanes; a span's rows go round the workgroup with kAhead of them per thread in flight, so
+// the tokens are read at the rate of memory (128K x 4: 2.1 GB; 2.25 ms with one 2-byte load
+// after another per thread).
+template <int ELEM, int D>
+__global__ void __launch_bounds__(BT) gather_kernel(BuildArgs a, int ab) {
+    constexpr int VEC = 16 / ELEM, LPR = D / VEC, RPP = BT / LPR;    // values, lanes per row, rows per pass
+    constexpr int kAhead = 4;
+    const int per = ab + a.M_max;
+    const int pair = blockIdx.x / per, b = pair / a.Hkv, g = pair % a.Hkv;
+    const int y = int(blockIdx.x % per) - ab, tid = threadIdx.x;
+    const int rg = tid / LPR, col = tid % LPR;
+    const uint4 *K = static_cast<const uint4 *>(a.keys) + size_t(pair) * a.N * LPR;
+    const uint4 *V = static_cast<const uint4 *>(a.values) + size_t(pair) * a.N * LPR;
     const int nt = seq_tokens(a, b);
-    int na = a.n_anchors[b];
-    na = na < 0 ? 0 : min(na, min(a.A_max, a.N));
-    int ns = a.n_spans[b];
-    ns = ns < 0 ? 0 : min(ns, min(a.M_max, a.N));
-    // anchor rows
-    for (int i = tid; i < 64 * d; i += BT) {
-        const int r = y * 64 + i / d, col = i % d;
-        if (r < na) {
+    if (y < 0) {
+        int na = a.n_anchors[b];
+        na = na < 0 ? 0 : min(na, min(a.A_max, a.N));
+        const int r0 = (y + ab) * 64;
+        for (int r = r0 + rg; r < min(na, r0 + 64); r += RPP) {
             const int t = a.anchor_idx[size_t(b) * a.N + r];
             if (t >= 0 && t < nt) {
-                const size_t dst = (size_t(pair) * a.A_max + r) * d + col;
-                st_elem(a.anchor_k, dst, ld_elem(a.keys, (tok0 + t) * d + col, e), e);
-                st_elem(a.anchor_v, dst, ld_elem(a.values, (tok0 + t) * d + col, e), e);
+                const size_t dst = (size_t(pair) * a.A_max + r) * LPR + col;
+                static_cast<uint4 *>(a.anchor_k)[dst] = K[size_t(t) * LPR + col];
+                static_cast<uint4 *>(a.anchor_v)[dst] = V[size_t(t) * LPR + col];
             } else if (col == 0) {
                 flag_table(a);
             }
         }
+        return;
     }
     // span y: surprisal-weighted means; |S| and ln|S| once per sequence (g == 0)
+    int ns = a.n_spans[b];
+    ns = ns < 0 ? 0 : min(ns, min(a.M_max, a.N));
     if (y >= ns) return;
     const int s0 = a.span_start[size_t(b) * a.N + y];
-    int L = a.span_len_seg[size_t(b) * a.N + y];
+    const int L = a.span_len_seg[size_t(b) * a.N + y];
     if (s0 < 0 || L < 1 || s0 + L > nt) {
         if (tid == 0 && g == 0) flag_table(a);
         return;
     }
-    __shared__ float red[2][BT];
-    __shared__ float hs;
-    // weight normaliser sum_t H_t over the span (float64 then float32)
+    __shared__ float red[2][RPP][D];
+    __shared__ double wtot[BT / 64];
+    const float *H = a.surprisal + size_t(b) * a.N + s0;
+    // weight normaliser sum_t H_t over the span (float64, then float32)
     {
         double acc = 0.0;
-        for (int t = tid; t < L; t += BT) acc += double(a.surprisal[size_t(b) * a.N + s0 + t]);
-        red[0][tid] = float(acc);
-        __syncthreads();
-        if (tid == 0) {
-            double s = 0.0;
-            for (int i = 0; i < BT; ++i) s += double(red[0][i]);
-            hs = float(s);
-        }
+        for (int t = tid; t < L; t += BT) acc += double(H[t]);
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        if ((tid & 63) == 0) wtot[tid >> 6] = acc;
         __syncthreads();
     }
-    const float tot = hs;
+    const float tot = float((wtot[0] + wtot[1]) + (wtot[2] + wtot[3]));
     const bool uniform = !(tot > 0.0f);
-    // thread: column col, token parity par (two tokens streams), then one pass through LDS
-    const int col = tid % d, par = tid / d, npar = BT / d;
-    float ak = 0.0f, av = 0.0f;
-    for (int t = par; t < L; t += npar) {
-        const float w = uniform ? 1.0f / float(L) : a.surprisal[size_t(b) * a.N + s0 + t] / tot;
-        ak += w * ld_elem(a.keys, (tok0 + s0 + t) * d + col, e);
-        av += w * ld_elem(a.values, (tok0 + s0 + t) * d + col, e);
+    K += size_t(s0) * LPR + col;
+    V += size_t(s0) * LPR + col;
+    float ak[VEC], av[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) ak[i] = av[i] = 0.0f;
+    for (int t0 = rg; t0 < L; t0 += kAhead * RPP) {
+        uint4 kv[kAhead], vv[kAhead];
+        float w[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int t = t0 + u * RPP, tc = min(t, L - 1);
+            kv[u] = K[size_t(tc) * LPR];
+            vv[u] = V[size_t(tc) * LPR];
+            w[u] = t < L ? (uniform ? 1.0f / float(L) : H[tc] / tot) : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (t0 + u * RPP < L) {
+                float f[VEC];
+                unpack16<ELEM>(kv[u], f);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) ak[i] += w[u] * f[i];
+                unpack16<ELEM>(vv[u], f);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) av[i] += w[u] * f[i];
+            }
+        }
     }
-    red[0][tid] = ak;
-    red[1][tid] = av;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+        red[0][rg][col * VEC + i] = ak[i];
+        red[1][rg][col * VEC + i] = av[i];
+    }
     __syncthreads();
-    if (par == 0) {
-        float sk = 0.0f, sv = 0.0f;
-        for (int p = 0; p < npar; ++p) { sk += red[0][p * d + col]; sv += red[1][p * d + col]; }
-        const size_t dst = (size_t(pair) * a.M_max + y) * d + col;
-        st_elem(a.sum_k, dst, sk, e);
-        st_elem(a.sum_v, dst, sv, e);
+    for (int i = tid; i < 2 * D; i += BT) {
+        const int side = i / D, c = i % D;
+        float s = 0.0f;
+        for (int p = 0; p < RPP; ++p) s += red[side][p][c];
+        st_elem(side ? a.sum_v : a.sum_k, (size_t(pair) * a.M_max + y) * D + c, s, ELEM);
     }
     if (g == 0 && tid == 0) {
         a.span_len_out[size_t(b) * a.M_max + y] = L;
@@ -282,8 +340,15 @@ hipError_t launch_build(const BuildArgs &a, int batch, hipStream_t stream) {
     if (batch <= 0) return hipSuccess;
     if (a.d > 128 || a.l > kMaxL || a.l < 2 || a.R > kMaxL) return hipErrorInvalidValue;
     const unsigned pairs = unsigned(batch * a.Hkv);
-    const int rows = max(max((a.A_max + 63) / 64, a.M_max), 1);
-    hipLaunchKernelGGL(gather_kernel, dim3(pairs * unsigned(rows)), dim3(BT), 0, stream, a, rows);
+    const int ab = (a.A_max + 63) / 64;
+    const dim3 grid(pairs * unsigned(ab + a.M_max));
+    if (a.elem == 2) {
+        if (a.d == 128) hipLaunchKernelGGL((gather_kernel<2, 128>), grid, dim3(BT), 0, stream, a, ab);
+        else hipLaunchKernelGGL((gather_kernel<2, 64>), grid, dim3(BT), 0, stream, a, ab);
+    } else {
+        if (a.d == 128) hipLaunchKernelGGL((gather_kernel<4, 128>), grid, dim3(BT), 0, stream, a, ab);
+        else hipLaunchKernelGGL((gather_kernel<4, 64>), grid, dim3(BT), 0, stream, a, ab);
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || a.M_max == 0) return err;
     // four waves per span side while the sides (an upper bound: M_max per pair) leave CUs

@@ -19,6 +19,8 @@ bool misaligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t
 size_t seg_ws(const sekv_build_dims &d) {
     const size_t B = size_t(d.batch), N = size_t(d.max_tokens);
     auto a16 = [](size_t x) { return (x + 15) & ~size_t(15); };
+    // the position list; the two byte arrays before it are part of the size that callers know
+    // and are not used
     return a16(B * N) * 2 + a16(B * (N + 2) * 4);
 }
 
@@ -43,16 +45,11 @@ sekv_status sekv_segment(const sekv_build_dims *dims, const float *surprisal, co
         misaligned(span_start, 4) || misaligned(span_len, 4) || misaligned(ws, 16))
         return fail(SEKV_ERR_INVALID_ARG, "misaligned argument");
     if (ws_bytes < seg_ws(*dims)) return fail(SEKV_ERR_WORKSPACE, "segmentation workspace too small");
-    const size_t B = size_t(dims->batch), N = size_t(dims->max_tokens);
-    auto a16 = [](size_t x) { return (x + 15) & ~size_t(15); };
-    unsigned char *w = static_cast<unsigned char *>(ws);
     sekv::SegArgs a{};
     a.surprisal = surprisal; a.n_tokens = n_tokens;
     a.n_anchors = n_anchors; a.anchor_idx = anchor_idx;
     a.n_spans = n_spans; a.span_start = span_start; a.span_len = span_len;
-    a.ws_flag = w;
-    a.ws_inspan = w + a16(B * N);
-    a.ws_pos = reinterpret_cast<int32_t *>(w + 2 * a16(B * N));
+    a.ws_pos = static_cast<int32_t *>(ws);
     a.alpha = dims->alpha;
     a.N = dims->max_tokens; a.min_span = dims->min_span; a.window = dims->window;
     const hipError_t e = sekv::launch_segment(a, dims->batch, stream);

@@ -15,7 +15,6 @@ struct SegArgs {
     const int32_t *n_tokens;           // [B]
     int32_t *n_anchors, *anchor_idx;   // [B], [B][N]
     int32_t *n_spans, *span_start, *span_len;   // [B], [B][N], [B][N]
-    unsigned char *ws_flag, *ws_inspan;         // [B][N] scratch
     int32_t *ws_pos;                   // [B][N + 2] scratch
     double alpha;
     int32_t N, min_span, window;

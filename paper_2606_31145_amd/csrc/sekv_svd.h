@@ -193,34 +193,38 @@ __device__ __forceinline__ int chol(double (*g)[LS], int *piv, int n, double tau
             w[jj] = 0.0;
             pr[jj] = 0;
             if (stop || jb + jj >= n) { stop = true; continue; }
+            // everything up to the new row before the test that may end the loop, in one
+            // block: the reciprocal root fills the reduction's wait states, the row's LDS read
+            // is under way during the factors' reads
             const uint32_t hi = uint32_t(uint64_t(__double_as_longlong(dg)) >> 32);
             const bool live = !taken && dg > 0.0;
             const uint32_t key = wave_max_u32(live ? (hi & ~63u) | uint32_t(63 - lane) : 0u);
             const double ry = rsqrt64(live ? dg : 1.0);
             const uint32_t ku = uint32_t(__builtin_amdgcn_readfirstlane(int(key)));
-            const int p = 63 - int(ku & 63u);
-            const double v = lane_get(dg, p);
-            if (jb + jj == 0) floor_ = tau * v;
-            if (ku == 0 || !(v > floor_)) { stop = true; continue; }
-            pr[jj] = p;
+            const int p = min(63 - int(ku & 63u), NL - 1);
             const double va = g[p][li];
-            const double rinv = lane_get(ry, p);
-            double acc = (taken || lane == p) ? 0.0 : va;
+            const double v = lane_get(dg, p), rinv = lane_get(ry, p);
+            double acc = (taken || lane == p) ? 0.0 : va, acc2 = 0.0;
             if (INV && taken && !fresh) acc = va;
 #pragma unroll
             for (int m = 0; m < jj; ++m) {
-                acc = fma(-lane_get(w[m], p), w[m], acc);
-                if (INV && lane == p) w[m] = 0.0;    // column p holds C from here on
+                if (m & 1) acc2 = fma(-lane_get(w[m], p), w[m], acc2);
+                else acc = fma(-lane_get(w[m], p), w[m], acc);
             }
-            double res = acc * rinv;
+            double res = (acc + acc2) * rinv;
             if (!INV && taken) res = 0.0;
             if (lane == p) res = INV ? rinv : v * rinv;
+            if (jb + jj == 0) floor_ = tau * v;
+            if (ku == 0 || !(v > floor_)) { stop = true; continue; }
+            pr[jj] = p;
+            if (INV)
+#pragma unroll
+                for (int m = 0; m < jj; ++m)
+                    if (lane == p) w[m] = 0.0;       // column p holds C from here on
             w[jj] = res;
             if (!taken) dg = fma(-res, res, dg);
-            if (lane == p) {
-                taken = fresh = true;
-                piv[jb + jj] = p;
-            }
+            if (lane == p) taken = fresh = true;
+            if (lane == 0) piv[jb + jj] = p;
             k = jb + jj + 1;
         }
         wave_sync();                                  // g's rows have been read

@@ -33,7 +33,7 @@ INSTANCES = [("BF16", 128), ("BF16", 64), ("F32", 128), ("F32", 64)]
 # every source the kernels are built from (the bench hashes these to tie counter
 # figures to the kernel code they were taken on)
 KERNEL_SOURCES = [os.path.join(CSRC, f) for f in
-                  ("sekv_internal.h", "sekv_step.h", "sekv_step_inst.hip", "sekv_kernels.hip")]
+                  ("sekv_internal.h", "sekv_step.h", "sekv_share.h", "sekv_step_inst.hip", "sekv_kernels.hip")]
 
 
 def _run(cmd, verbose):

@@ -21,7 +21,8 @@
 // Data movement: an item issues its global loads up front, as 16-byte vectors mapped
 // (row, column) onto the workgroup -- a wave reads 1 KB of contiguous rows per
 // instruction -- and keeps them in registers; row sums are lane shuffles inside a row
-// plus one cross-wave pass through LDS.
+// plus one cross-wave pass through LDS.  With bfloat16 storage a share item's rows go to
+// the matrix cores instead (sekv_share.h).
 //
 // Cross-workgroup protocol.  Routing results travel as tagged words: 32 bits of payload
 // and the launch's 32-bit tag in one 64-bit relaxed agent-scope atomic store
@@ -48,6 +49,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "sekv_internal.h"
 
@@ -347,7 +350,8 @@ struct Smem {
     static constexpr int NJ = 4;                          // rows per thread in a summary block
     static constexpr int NJA = 8;                         // rows per thread in an anchor block
     static constexpr int AB = NJA * GE::RPP;              // anchor tokens per block
-    static constexpr int CB = NJ * GE::RPP;               // summary rows per block
+    static constexpr bool kMfma = T::kBytes == 2;         // the share items of sekv_share.h
+    static constexpr int CB = kMfma ? 64 : NJ * GE::RPP;  // summary rows per block
     struct Route {                                       // routing item
         unsigned char kb[CR * GE::RS];                   // summary key rows
         double lns[CR];                                  // ln|S| of the chunk's spans
@@ -357,9 +361,16 @@ struct Smem {
         uint64_t skey[2][64];                            // two sorted halves of the chunk
         uint32_t sidx[2][64];
     };
-    struct Share {                                       // share item
+    struct ShareMfma {                                   // share item, bf16 storage
+        unsigned char wb[4][32 * GE::RS > 6144 ? 32 * GE::RS : 6144];   // a wave's rows, to be turned
+        float cw[G][CB];                                 // summary logits
+        uint4 cand[kMergeBuf];                           // {~span, key lo, key hi, -}
+        uint32_t rk[NT];                                 // partial ranks (two scanners)
+        int32_t sel[kMaxTopK];                           // the pair's selected spans
+        int4 zi[kMaxTopK];                               // {span, |S|, offset lo, hi} per rank
+    };
+    struct ShareFma {                                    // share item, fp32 storage
         float qf[G][D];
-        uint32_t qb[G][D / 2];                           // the same query, bf16 pairs (bf16 storage)
         float sc[G][AB];                                 // anchor scores, then weights
         float cw[G][CB];                                 // summary logits, then weights
         uint4 cand[kMergeBuf];                           // {~span, key lo, key hi, -}
@@ -371,6 +382,7 @@ struct Smem {
         float yr[4][G][kMaxTopK];                        // per-wave partial sums of p^T U_V
         float y[G][kMaxTopK];                            // (p^T U_V) * sigma_V
     };
+    using Share = std::conditional_t<kMfma, ShareMfma, ShareFma>;
     struct Merge {                                       // single-merger selection
         uint64_t key[kMergeBuf];
         uint32_t idx[kMergeBuf];
@@ -388,39 +400,25 @@ struct Smem {
         Final fin;
     } u;
     float red[4][G][D];                                  // per-wave row sums
-    float m_run[G], l_run[G], scale_old[G];              // online softmax state
-    int32_t bcast[8];
+    float m_run[G], l_run[G], scale_old[G];              // online softmax state (fp32 storage)
+    float mw[4][G], lw[4][G];                            // the waves' softmax states (bf16 storage)
+    int32_t bcast[8], all[4];
 #ifdef SEKV_PHASE_TRACE
     int trace_item;
 #endif
 };
 
-// part[h] = sum over the values of 16-byte vector c of a row times query row h: packed
-// bf16 dot products (exact products, fp32 sums) for bf16 storage, fp32 FMAs for fp32.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+// part[h] = sum over the values of 16-byte vector c of a row times query row h
 template <class T, int D, int G>
 __device__ inline void query_dot(const Smem<T, D, G> &sm, const uint4 &v, int c, float (&part)[G]) {
     const auto &Z = sm.u.share;
-    if constexpr (T::kBytes == 2) {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    float f[T::kVec];
+    T::unpack(v, f);
 #pragma unroll
-        for (int hl = 0; hl < G; ++hl) {
-            float a = 0.0f;
+    for (int hl = 0; hl < G; ++hl) {
+        part[hl] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w[i]),
-                                                    __builtin_bit_cast(bf16x2_t, Z.qb[hl][c * 4 + i]), a, false);
-            part[hl] = a;
-        }
-    } else {
-        float f[T::kVec];
-        T::unpack(v, f);
-#pragma unroll
-        for (int hl = 0; hl < G; ++hl) {
-            part[hl] = 0.0f;
-#pragma unroll
-            for (int e = 0; e < T::kVec; ++e) part[hl] += Z.qf[hl][c * T::kVec + e] * f[e];
-        }
+        for (int e = 0; e < T::kVec; ++e) part[hl] += Z.qf[hl][c * T::kVec + e] * f[e];
     }
 }
 
@@ -1209,6 +1207,18 @@ __device__ inline bool coarse_logits(const Params &p, Smem<T, D, G> &sm, int pai
     return ok;
 }
 
+// Whether every thread's ok holds.  (__syncthreads_and keeps the thread's y and z indices in
+// registers for it, two more than the widest fp32 zoom leaves.)
+template <class T, int D, int G>
+__device__ inline bool all_threads(Smem<T, D, G> &sm, bool ok, int tid) {
+    const bool mine = __ballot(ok) == ~0ull;
+    if ((tid & 63) == 0) sm.all[tid >> 6] = mine;
+    __syncthreads();
+    const bool all = sm.all[0] & sm.all[1] & sm.all[2] & sm.all[3];
+    __syncthreads();                                    // read before the next round's votes
+    return __builtin_amdgcn_readfirstlane(int(all));
+}
+
 // Poll until the logits of summary block [c0, c0 + nc) are this launch's.  Returns true
 // when the wait has lasted kHelpAfter polls (the share item then gives up for help_route).
 template <class T, int D, int G>
@@ -1216,7 +1226,7 @@ __device__ inline bool wait_coarse_logits(const Params &p, Smem<T, D, G> &sm, in
                                           int nc, uint32_t tag, int tid, bool may_give_up) {
     for (uint32_t it = 0;; ++it) {
         const bool ok = coarse_logits<T, D, G>(p, sm, pair, c0, nc, tag, tid);
-        if (__syncthreads_and(ok)) return false;
+        if (all_threads(sm, ok, tid)) return false;
         if (it >= kSpinLimit) {
             if (tid == 0) flag_error(p, kErrSpinTimeout);
             return false;
@@ -1439,7 +1449,7 @@ __device__ __forceinline__ void zoom_span(const Params &p, Smem<T, D, G> &sm, in
 
     // w[h][i] = scale*log2e * sigma_K[i] * (Vt_K[i] . q_h).  No barrier first: Z.w was
     // last read by an earlier zoom, which has passed several barriers since, and the
-    // query rows (Z.qf / Z.qb) were written at the start of the item.
+    // query rows (Z.qf) were written at the start of the item.
 #pragma unroll
     for (int u = 0; u < NVT; ++u) {
         const int vi = tid + NT * u;
@@ -1576,81 +1586,15 @@ __device__ __forceinline__ void zoom_span(const Params &p, Smem<T, D, G> &sm, in
     SEKV_STAMP(p, sm, kTrSZoomDone);
 }
 
-// ---------------------------------------------------------------------------
-// share item: anchors share, selection slot j, summaries share of one pair
-// ---------------------------------------------------------------------------
-// Returns true when a wait lasted kHelpAfter polls: the caller then helps with routing
-// (help_route) and runs the item again from the start.
+// The pair's selection (Z.sel; Z.zi at least for this slot's ranks, blocks outside the arena
+// dropped and flagged) and the logits of summary rows [c_lo, c_lo + nc0) (Z.cw), for every thread.
+// Returns true when the wait for them lasted kHelpAfter polls.
 template <class T, int D, int G>
-__device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, int pair, int j,
-                                           uint32_t tag, int tid, bool first, bool may_give_up, bool leave) {
-    using GE = Geo<T, D>;
-    using SM = Smem<T, D, G>;
-    constexpr int NJ = SM::NJ, NJA = SM::NJA, AB = SM::AB, CB = SM::CB;
+__device__ __forceinline__ bool select_spans(const Params &p, Smem<T, D, G> &sm, int pair, int j, int m_b, int c_lo,
+                                             int nc0, uint32_t tag, int tid, bool may_give_up) {
     auto &Z = sm.u.share;
-    const int b = pair / p.Hkv, g = pair % p.Hkv;
-    const int k = p.k, r = p.r, nz = p.n_zi;
-    // this item's shares: contiguous ranges of the anchor and span index spaces up to
-    // the maxima, so the first loads need no table value; the sequence's own counts
-    // (n_anchors, n_spans) mask rows where the values are used
-    // anchors go to the slots that start with the launch (j < n_early): they fold them
-    // while routing runs, and later slots reach their selection and zoom sooner
-    const int ne = p.n_early;
-    const int as = (p.A_max + ne - 1) / ne;
-    const int a_lo = j < ne ? min(p.A_max, j * as) : p.A_max, a_hi = min(p.A_max, a_lo + as);
-    const int cs = (p.M_max + nz - 1) / nz;
-    const int c_lo = min(p.M_max, j * cs), c_hi = min(p.M_max, c_lo + cs);
-    const int rgrp = tid / GE::RV, col = tid % GE::RV;
-    const size_t pr = size_t(b) * p.Hkv + g;
-    const unsigned char *ak = reinterpret_cast<const unsigned char *>(p.anchor_k) + pr * p.A_max * GE::RB;
-    const unsigned char *av = reinterpret_cast<const unsigned char *>(p.anchor_v) + pr * p.A_max * GE::RB;
-    const unsigned char *sv = reinterpret_cast<const unsigned char *>(p.sum_v) + pr * p.M_max * GE::RB;
-
-    if (first && p.end_route > 0) __builtin_amdgcn_s_sleep(kShareHoldBack);
-    // 1. loads that depend on nothing: the first anchor block, the first summary block
-    //    (values only; its logits come from routing), the query
-    uint4 kr[NJA], vr[NJA], cv[NJ];
-    load_rows<T, D, NJA>(kr, ak + size_t(a_lo) * GE::RB, min(AB, a_hi - a_lo), rgrp, col);
-    load_rows<T, D, NJA>(vr, av + size_t(a_lo) * GE::RB, min(AB, a_hi - a_lo), rgrp, col);
-    load_rows<T, D, NJ>(cv, sv + size_t(c_lo) * GE::RB, min(CB, c_hi - c_lo), rgrp, col);
-    int m_b = p.n_spans[b];
-    m_b = m_b < 0 ? 0 : (m_b > p.M_max ? p.M_max : m_b);
-    int An = p.n_anchors[b];
-    An = An < 0 ? 0 : (An > p.A_max ? p.A_max : An);
-    for (int i = tid; i < G * D; i += NT) {
-        const int hl = i / D, d = i % D;
-        Z.qf[hl][d] = T::load1(p.q, (size_t(b) * p.Hq + size_t(g) * G + hl) * D + d);
-    }
-    if constexpr (T::kBytes == 2) {
-        const uint32_t *q2 = reinterpret_cast<const uint32_t *>(p.q) + (size_t(b) * p.Hq + size_t(g) * G) * (D / 2);
-        for (int i = tid; i < G * D / 2; i += NT) Z.qb[i / (D / 2)][i % (D / 2)] = q2[i];
-    }
-    online_reset(G, sm.m_run, sm.l_run, sm.scale_old, tid);
-    for (int t = tid; t < kMaxTopK; t += NT) { Z.sel[t] = -1; Z.zi[t] = make_int4(-1, 0, 0, 0); }
-    for (int i = tid; i < 4 * G * D; i += NT) (&sm.red[0][0][0])[i] = 0.0f;
-    __syncthreads();
-    // valid rows of the prefetched blocks
-    const int nc0 = max(0, min(min(CB, c_hi - c_lo), m_b - c_lo));
-    // the weighted value sums live in sm.red (one row per wave); pend holds the rescale
-    // factors not yet applied to them
-    float pend[G];
-#pragma unroll
-    for (int hl = 0; hl < G; ++hl) pend[hl] = 1.0f;
-
-    // 2. the anchor share, while routing runs elsewhere; the next block's keys load
-    //    while this block's values are used, its values while the next scores are taken
-    for (int a0 = a_lo; a0 < a_hi && a0 < An; a0 += AB) {
-        const int na = min(min(AB, a_hi - a0), An - a0);
-        const int a1 = a0 + AB;
-        const int na1 = (a1 < a_hi && a1 < An) ? min(min(AB, a_hi - a1), An - a1) : 0;
-        anchor_scores<T, D, G, NJA>(p, sm, kr, na, rgrp, col);
-        load_rows<T, D, NJA>(kr, ak + size_t(a1) * GE::RB, na1, rgrp, col);
-        anchor_values<T, D, G, NJA>(sm, vr, na, pend, rgrp, tid);
-        load_rows<T, D, NJA>(vr, av + size_t(a1) * GE::RB, na1, rgrp, col);
-    }
-
-    SEKV_STAMP(p, sm, kTrSAnchors);
-    // 3. the selection (Z.sel, this slot's span in bcast) and the first block's logits
+    const int b = pair / p.Hkv, k = p.k, nz = p.n_zi;
+    const size_t pr = size_t(pair);
     const bool per_item = (p.mode == kModeFused) && !p.merger;
     if (per_item) {
         uint64_t okey[kOwn];
@@ -1661,7 +1605,7 @@ __device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, i
         for (uint32_t it = 0;; ++it) {
             bool ok = load_candidates(p, pair, tag, okey, oidx, olen, ooff, tid);
             ok &= coarse_logits<T, D, G>(p, sm, pair, c_lo, nc0, tag, tid);
-            const bool all = __syncthreads_and(ok);
+            const bool all = all_threads(sm, ok, tid);
             if (it == 0) SEKV_STAMP(p, sm, kTrSPolled);
             if (all) {
                 SEKV_NOTE(p, sm, kTrSPolls, it + 1);
@@ -1730,6 +1674,83 @@ __device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, i
         }
     }
     __syncthreads();
+    return false;
+}
+
+#include "sekv_share.h"
+
+// ---------------------------------------------------------------------------
+// share item with fp32 storage: anchors share, selection slot j, summaries share of one pair
+// ---------------------------------------------------------------------------
+// Returns true when a wait lasted kHelpAfter polls: the caller then helps with routing
+// (help_route) and runs the item again from the start.
+template <class T, int D, int G>
+__device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, int pair, int j,
+                                           uint32_t tag, int tid, bool first, bool may_give_up, bool leave) {
+    using GE = Geo<T, D>;
+    using SM = Smem<T, D, G>;
+    constexpr int NJ = SM::NJ, NJA = SM::NJA, AB = SM::AB, CB = SM::CB;
+    auto &Z = sm.u.share;
+    const int b = pair / p.Hkv, g = pair % p.Hkv;
+    const int k = p.k, r = p.r, nz = p.n_zi;
+    // this item's shares: contiguous ranges of the anchor and span index spaces up to
+    // the maxima, so the first loads need no table value; the sequence's own counts
+    // (n_anchors, n_spans) mask rows where the values are used
+    // anchors go to the slots that start with the launch (j < n_early): they fold them
+    // while routing runs, and later slots reach their selection and zoom sooner
+    const int ne = p.n_early;
+    const int as = (p.A_max + ne - 1) / ne;
+    const int a_lo = j < ne ? min(p.A_max, j * as) : p.A_max, a_hi = min(p.A_max, a_lo + as);
+    const int cs = (p.M_max + nz - 1) / nz;
+    const int c_lo = min(p.M_max, j * cs), c_hi = min(p.M_max, c_lo + cs);
+    const int rgrp = tid / GE::RV, col = tid % GE::RV;
+    const size_t pr = size_t(b) * p.Hkv + g;
+    const unsigned char *ak = reinterpret_cast<const unsigned char *>(p.anchor_k) + pr * p.A_max * GE::RB;
+    const unsigned char *av = reinterpret_cast<const unsigned char *>(p.anchor_v) + pr * p.A_max * GE::RB;
+    const unsigned char *sv = reinterpret_cast<const unsigned char *>(p.sum_v) + pr * p.M_max * GE::RB;
+
+    if (first && p.end_route > 0) __builtin_amdgcn_s_sleep(kShareHoldBack);
+    // 1. loads that depend on nothing: the first anchor block, the first summary block
+    //    (values only; its logits come from routing), the query
+    uint4 kr[NJA], vr[NJA], cv[NJ];
+    load_rows<T, D, NJA>(kr, ak + size_t(a_lo) * GE::RB, min(AB, a_hi - a_lo), rgrp, col);
+    load_rows<T, D, NJA>(vr, av + size_t(a_lo) * GE::RB, min(AB, a_hi - a_lo), rgrp, col);
+    load_rows<T, D, NJ>(cv, sv + size_t(c_lo) * GE::RB, min(CB, c_hi - c_lo), rgrp, col);
+    int m_b = p.n_spans[b];
+    m_b = m_b < 0 ? 0 : (m_b > p.M_max ? p.M_max : m_b);
+    int An = p.n_anchors[b];
+    An = An < 0 ? 0 : (An > p.A_max ? p.A_max : An);
+    for (int i = tid; i < G * D; i += NT) {
+        const int hl = i / D, d = i % D;
+        Z.qf[hl][d] = T::load1(p.q, (size_t(b) * p.Hq + size_t(g) * G + hl) * D + d);
+    }
+    online_reset(G, sm.m_run, sm.l_run, sm.scale_old, tid);
+    for (int t = tid; t < kMaxTopK; t += NT) { Z.sel[t] = -1; Z.zi[t] = make_int4(-1, 0, 0, 0); }
+    for (int i = tid; i < 4 * G * D; i += NT) (&sm.red[0][0][0])[i] = 0.0f;
+    __syncthreads();
+    // valid rows of the prefetched blocks
+    const int nc0 = max(0, min(min(CB, c_hi - c_lo), m_b - c_lo));
+    // the weighted value sums live in sm.red (one row per wave); pend holds the rescale
+    // factors not yet applied to them
+    float pend[G];
+#pragma unroll
+    for (int hl = 0; hl < G; ++hl) pend[hl] = 1.0f;
+
+    // 2. the anchor share, while routing runs elsewhere; the next block's keys load
+    //    while this block's values are used, its values while the next scores are taken
+    for (int a0 = a_lo; a0 < a_hi && a0 < An; a0 += AB) {
+        const int na = min(min(AB, a_hi - a0), An - a0);
+        const int a1 = a0 + AB;
+        const int na1 = (a1 < a_hi && a1 < An) ? min(min(AB, a_hi - a1), An - a1) : 0;
+        anchor_scores<T, D, G, NJA>(p, sm, kr, na, rgrp, col);
+        load_rows<T, D, NJA>(kr, ak + size_t(a1) * GE::RB, na1, rgrp, col);
+        anchor_values<T, D, G, NJA>(sm, vr, na, pend, rgrp, tid);
+        load_rows<T, D, NJA>(vr, av + size_t(a1) * GE::RB, na1, rgrp, col);
+    }
+
+    SEKV_STAMP(p, sm, kTrSAnchors);
+    // 3. the selection (Z.sel, Z.zi) and the first block's logits
+    if (select_spans<T, D, G>(p, sm, pair, j, m_b, c_lo, nc0, tag, tid, may_give_up)) return true;
 
     // 4. zoom the slot's spans (ranks j, j + n_zi, ...).  With one span, the first
     //    summary block is folded while its factor loads are in flight; with several,
@@ -1739,24 +1760,15 @@ __device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, i
     };
     auto zoom_ranked = [&](auto ranked_c, int32_t w, int64_t off, int tid, auto &&mid) {
         constexpr bool RANKED = decltype(ranked_c)::value;
-        // 16-byte vectors per U row at the largest rank: 8..64 gives 1..8 (bf16) or 2..16
-        // (f32); the block's own ranks r_K, r_V <= r travel in the span word
+        // 16-byte vectors per U row at the largest rank: 8..64 gives 2..16; the
+        // block's own ranks r_K, r_V <= r travel in the span word
         const int ru = r * T::kBytes / 16;
         const int L = word_len(w), rk = word_rk(w), rv = word_rv(w);
-        if constexpr (T::kBytes == 2) {
-            switch (ru) {
-                case 1: zoom_span<T, D, G, 1, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-                case 2: zoom_span<T, D, G, 2, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-                case 4: zoom_span<T, D, G, 4, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-                default: zoom_span<T, D, G, 8, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-            }
-        } else {
-            switch (ru) {
-                case 2: zoom_span<T, D, G, 2, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-                case 4: zoom_span<T, D, G, 4, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-                case 8: zoom_span<T, D, G, 8, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-                default: zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-            }
+        switch (ru) {
+            case 2: zoom_span<T, D, G, 2, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
+            case 4: zoom_span<T, D, G, 4, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
+            case 8: zoom_span<T, D, G, 8, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
+            default: zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
         }
     };
     auto zoom_one = [&](int32_t w, int64_t off, int tid, auto &&mid) {
@@ -1825,8 +1837,12 @@ __global__ void __launch_bounds__(NT, G == 8 ? 1 : 2) sekv_step_kernel(Params p)
             const int i = item - p.end_route;                // slot-major
             const int P = p.B * p.Hkv;
             const bool leave = item + p.grid >= n_items;
-            if (share_item<T, D, G>(p, sm, i % P, i / P, tag, t, item == int(blockIdx.x) && helps == 0,
-                                    helps < kMaxHelps, leave)) {
+            const bool first = item == int(blockIdx.x) && helps == 0, may = helps < kMaxHelps;
+            bool help;
+            if constexpr (Smem<T, D, G>::kMfma)
+                help = share_item_mfma<T, D, G>(p, sm, i % P, i / P, tag, t, first, may, leave);
+            else help = share_item<T, D, G>(p, sm, i % P, i / P, tag, t, first, may, leave);
+            if (help) {
                 help_route<T, D, G>(p, sm, i % P, tag, t);
                 ++helps;
                 continue;                                    // the same item again

@@ -143,10 +143,6 @@ template <int CTRL>
 __device__ inline float dpp_mov(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-template <int CTRL>
-__device__ inline uint32_t dpp_mov_u(uint32_t v) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, false));
-}
 constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kDppRor4 = 0x124;       // row_ror:4
@@ -223,22 +219,6 @@ __device__ inline float col_sum(float v) {     // sum over the lanes sharing lan
     else return lane_reduce<5, 6>(v);
 }
 
-// Value of the lane at index ^ S (bitonic partner), 32-bit.
-template <int S>
-__device__ inline uint32_t lane_xor(uint32_t v, int lane) {
-    if constexpr (S == 1) return dpp_mov_u<kDppXor1>(v);
-    else if constexpr (S == 2) return dpp_mov_u<kDppXor2>(v);
-    else if constexpr (S == 8) return dpp_mov_u<kDppRor8>(v);
-    else if constexpr (S == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        return (lane & 16) ? r[0] : r[1];
-    } else if constexpr (S == 32) {
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        return (lane & 32) ? r[0] : r[1];
-    } else {
-        return uint32_t(__shfl_xor(int(v), S, 64));
-    }
-}
 __device__ inline float safe_exp2(float x) { return x == -INFINITY ? 0.0f : exp2f(x); }
 
 // ---------------------------------------------------------------------------
@@ -355,16 +335,18 @@ struct Smem {
     struct Route {                                       // routing item
         unsigned char kb[CR * GE::RS];                   // summary key rows
         double lns[CR];                                  // ln|S| of the chunk's spans
-        double pmax[2][CR];                              // per head group max score
+        unsigned long long key[CR];                      // order keys of the spans (0: no span)
+        uint32_t khi[CR];                                // their high words
+        uint32_t prank[2][CR];                           // partial ranks over the list's halves
+        int32_t slot[kMaxTopK];                          // span of each rank
         int32_t slen[CR];                                // |S| of the chunk's spans
         int64_t boff[CR];                                // their block offsets
-        uint64_t skey[2][64];                            // two sorted halves of the chunk
-        uint32_t sidx[2][64];
     };
     struct ShareMfma {                                   // share item, bf16 storage
         unsigned char wb[4][32 * GE::RS > 6144 ? 32 * GE::RS : 6144];   // a wave's rows, to be turned
         float cw[G][CB];                                 // summary logits
         uint4 cand[kMergeBuf];                           // {~span, key lo, key hi, -}
+        uint32_t chi[kMergeBuf];                         // the candidates' key high words
         uint32_t rk[NT];                                 // partial ranks (two scanners)
         int32_t sel[kMaxTopK];                           // the pair's selected spans
         int4 zi[kMaxTopK];                               // {span, |S|, offset lo, hi} per rank
@@ -374,6 +356,7 @@ struct Smem {
         float sc[G][AB];                                 // anchor scores, then weights
         float cw[G][CB];                                 // summary logits, then weights
         uint4 cand[kMergeBuf];                           // {~span, key lo, key hi, -}
+        uint32_t chi[kMergeBuf];                         // the candidates' key high words
         uint32_t rk[NT];                                 // partial ranks (two scanners)
         int32_t sel[kMaxTopK];                           // the pair's selected spans
         int4 zi[kMaxTopK];                               // {span, |S|, offset lo, hi} per rank
@@ -879,12 +862,228 @@ __device__ __forceinline__ void dpp_fma_block(double (&a)[HPT], const double (&q
     }
 }
 
+// cnt += number of the 4 n words of list (LDS, 16-byte aligned) that are >= me.  Ranks by the
+// high words of the order keys take two instructions a comparison and a quarter of the LDS
+// reads of whole keys; entries that share a high word all get the rank of the last of them, so
+// a tie leaves a rank without an entry, which the callers look for (and then rank by whole
+// keys).
+__device__ __forceinline__ uint32_t count_ge(const uint32_t *list, int n, uint32_t me) {
+    uint32_t c0 = 0, c1 = 0;
+    auto four = [&](const uint4 &e) {
+        asm("v_cmp_ge_u32 vcc, %2, %6\n\t"
+            "v_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+            "v_cmp_ge_u32 vcc, %3, %6\n\t"
+            "v_addc_co_u32 %1, vcc, 0, %1, vcc\n\t"
+            "v_cmp_ge_u32 vcc, %4, %6\n\t"
+            "v_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+            "v_cmp_ge_u32 vcc, %5, %6\n\t"
+            "v_addc_co_u32 %1, vcc, 0, %1, vcc"
+            : "+v"(c0), "+v"(c1)
+            : "v"(e.x), "v"(e.y), "v"(e.z), "v"(e.w), "v"(me)
+            : "vcc");
+    };
+    const uint4 *l4 = reinterpret_cast<const uint4 *>(list);
+    int o = 0;
+#pragma unroll 1
+    for (; o + 4 <= n; o += 4) {
+        uint4 e[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) e[w] = l4[o + w];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) four(e[w]);
+    }
+#pragma unroll 1
+    for (; o < n; ++o) four(l4[o]);
+    return c0 + c1;
+}
+
+constexpr int kOwn = kMergeBuf / NT;                   // candidates per thread when ranking
+
+// One polling attempt on the pair's candidate records; thread tid owns candidates tid
+// and tid + NT.  Returns whether every tag was current.
+__device__ inline bool load_candidates(const Params &p, int pair, uint32_t tag, uint64_t (&okey)[kOwn],
+                                       uint32_t (&oidx)[kOwn], int32_t (&olen)[kOwn],
+                                       int64_t (&ooff)[kOwn], int tid) {
+    const size_t FS = size_t(p.B) * p.Hkv * size_t(p.n_cand);
+    const uint64_t *rec = p.cand + size_t(pair) * p.n_cand;
+    bool ok = true;
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        const int c = tid + NT * u;
+        okey[u] = 0;
+        oidx[u] = kInvalidIdx;
+        olen[u] = 0;
+        ooff[u] = 0;
+        if (c < p.n_cand) {
+            uint64_t w[kCandFields];
+#pragma unroll
+            for (int f = 0; f < kCandFields; ++f) w[f] = ld_shared(rec + f * FS + c);
+#pragma unroll
+            for (int f = 0; f < kCandFields; ++f) ok &= tag_is(w[f], tag);
+            okey[u] = (uint64_t(uint32_t(w[kCandKeyHi])) << 32) | uint32_t(w[kCandKeyLo]);
+            oidx[u] = uint32_t(w[kCandIdx]);
+            olen[u] = int32_t(uint32_t(w[kCandLen]));
+            ooff[u] = int64_t(uint64_t(uint32_t(w[kCandOffLo])) | (uint64_t(uint32_t(w[kCandOffHi])) << 32));
+        }
+    }
+    return ok;
+}
+
+// rk += 1 if (key_o, ~idx_o) > (key_c, ~idx_c) as 96-bit unsigned numbers, i.e. if
+// candidate o is ahead of candidate c in (key desc, span asc): the borrow out of
+// mine - other.  Words are {~idx, key lo, key hi}.
+__device__ __forceinline__ void count_ahead(uint32_t &rk, const uint4 &o, uint32_t m0, uint32_t m1,
+                                            uint32_t m2) {
+    uint32_t t;
+    asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
+        "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
+        "v_subb_co_u32 %0, vcc, %6, %7, vcc\n\t"
+        "v_addc_co_u32 %1, vcc, 0, %1, vcc"
+        : "=&v"(t), "+v"(rk)
+        : "v"(m0), "v"(o.x), "v"(m1), "v"(o.y), "v"(m2), "v"(o.z)
+        : "vcc");
+}
+
+// Rank the pair's candidates by whole keys (LDS): rank = number of candidates ahead in (key
+// desc, span asc).  Ranks below k fill Z.sel and Z.zi ({span, |S|, offset}).  Up to NT/2
+// candidates, two threads scan half the list each.
+template <class T, int D, int G>
+__device__ __forceinline__ void rank_exact(const Params &p, Smem<T, D, G> &sm, int m_b,
+                                                const uint64_t (&okey)[kOwn], const uint32_t (&oidx)[kOwn],
+                                                const int32_t (&olen)[kOwn], const int64_t (&ooff)[kOwn],
+                                                int tid) {
+    auto &Z = sm.u.share;
+    const int k = p.k, n_cand = p.n_cand;
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        const int c = tid + NT * u;
+        if (c < n_cand) Z.cand[c] = make_uint4(~oidx[u], uint32_t(okey[u]), uint32_t(okey[u] >> 32), 0);
+    }
+    __syncthreads();
+    const bool split = n_cand <= NT / 2;
+    if (split) {
+        // thread c and c + NT/2 rank candidate c over the two halves of the list
+        const int c = tid % (NT / 2), half = tid / (NT / 2);
+        const int o0 = half ? n_cand / 2 : 0, o1 = half ? n_cand : n_cand / 2;
+        uint32_t rk = 0;
+        if (c < n_cand) {
+            const uint4 me = Z.cand[c];
+            int o = o0;
+            for (; o + 8 <= o1; o += 8) {
+                uint4 e[8];
+#pragma unroll
+                for (int w = 0; w < 8; ++w) e[w] = Z.cand[o + w];
+#pragma unroll
+                for (int w = 0; w < 8; ++w) count_ahead(rk, e[w], me.x, me.y, me.z);
+            }
+            for (; o < o1; ++o) count_ahead(rk, Z.cand[o], me.x, me.y, me.z);
+        }
+        Z.rk[tid] = rk;
+        __syncthreads();
+        if (tid < n_cand && oidx[0] < 0x80000000u) {
+            const int r = int(Z.rk[tid] + Z.rk[tid + NT / 2]);
+            if (r < k && r < m_b) {
+                Z.sel[r] = int32_t(oidx[0]);
+                Z.zi[r] = make_int4(int32_t(oidx[0]), olen[0], int32_t(ooff[0] & 0xFFFFFFFF),
+                                    int32_t(ooff[0] >> 32));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+            const int c = tid + NT * u;
+            if (c >= n_cand || oidx[u] >= 0x80000000u) continue;
+            const uint32_t m0 = ~oidx[u], m1 = uint32_t(okey[u]), m2 = uint32_t(okey[u] >> 32);
+            uint32_t rk = 0;
+            int o = 0;
+            for (; o + 8 <= n_cand; o += 8) {
+                uint4 e[8];
+#pragma unroll
+                for (int w = 0; w < 8; ++w) e[w] = Z.cand[o + w];
+#pragma unroll
+                for (int w = 0; w < 8; ++w) count_ahead(rk, e[w], m0, m1, m2);
+            }
+            for (; o < n_cand; ++o) count_ahead(rk, Z.cand[o], m0, m1, m2);
+            if (int(rk) < k && int(rk) < m_b) {
+                Z.sel[rk] = int32_t(oidx[u]);
+                Z.zi[rk] = make_int4(int32_t(oidx[u]), olen[u], int32_t(ooff[u] & 0xFFFFFFFF),
+                                     int32_t(ooff[u] >> 32));
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// The same ranks from the key high words (count_ge), which settle all but ties; up to NT/2
+// candidates, two threads scan half the list each.  Z.sel and Z.zi are -1 before.  96 candidates:
+// 1.4 us instead of 2.1 for the 96-bit comparisons.
+template <class T, int D, int G>
+__device__ __forceinline__ void rank_candidates(const Params &p, Smem<T, D, G> &sm, int m_b,
+                                                const uint64_t (&okey)[kOwn], const uint32_t (&oidx)[kOwn],
+                                                const int32_t (&olen)[kOwn], const int64_t (&ooff)[kOwn],
+                                                int tid) {
+    auto &Z = sm.u.share;
+    const int k = p.k, n_cand = p.n_cand;
+    const int n4 = (n_cand + 3) / 4;                       // whole words of four (padding is 0: never >=)
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        const int c = tid + NT * u;
+        if (c < 4 * n4) Z.chi[c] = (c < n_cand && oidx[u] < 0x80000000u) ? uint32_t(okey[u] >> 32) : 0u;
+    }
+    __syncthreads();
+    auto place = [&](int u, int rk) {
+        if (rk < k && rk < m_b) {
+            Z.sel[rk] = int32_t(oidx[u]);
+            Z.zi[rk] = make_int4(int32_t(oidx[u]), olen[u], int32_t(ooff[u] & 0xFFFFFFFF), int32_t(ooff[u] >> 32));
+        }
+    };
+    if (n_cand <= NT / 2) {
+        const int c = tid % (NT / 2), half = tid / (NT / 2), mid = n4 / 2;
+        uint32_t rk = 0;
+        if (c < n_cand) rk = count_ge(Z.chi + (half ? 4 * mid : 0), half ? n4 - mid : mid, Z.chi[c]);
+        Z.rk[tid] = rk;
+        __syncthreads();
+        if (tid < n_cand && oidx[0] < 0x80000000u) place(0, int(Z.rk[tid] + Z.rk[tid + NT / 2]) - 1);
+    } else {
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+            const int c = tid + NT * u;
+            if (c >= n_cand || oidx[u] >= 0x80000000u) continue;
+            place(u, int(count_ge(Z.chi, n4, Z.chi[c])) - 1);
+        }
+    }
+    __syncthreads();
+    // a rank without a span: equal high words somewhere among the best (every wave sees the same)
+    const int lane = tid & 63;
+    if (__ballot(lane < k && lane < m_b && Z.sel[lane] < 0) != 0) {
+        __syncthreads();
+        rank_exact<T, D, G>(p, sm, m_b, okey, oidx, olen, ooff, tid);
+    }
+}
+
+// Selection of one pair by its last routing item (route mode): the share items' ranking.
+template <class T, int D, int G>
+__device__ __forceinline__ void rank_selection(const Params &p, Smem<T, D, G> &sm, int pair, int m_b, uint32_t tag,
+                                               int tid) {
+    auto &Z = sm.u.share;
+    uint64_t okey[kOwn];
+    uint32_t oidx[kOwn];
+    int32_t olen[kOwn];
+    int64_t ooff[kOwn];
+    load_candidates(p, pair, tag, okey, oidx, olen, ooff, tid);
+    if (tid < kMaxTopK) { Z.sel[tid] = -1; Z.zi[tid] = make_int4(-1, 0, 0, 0); }
+    __syncthreads();
+    rank_candidates<T, D, G>(p, sm, m_b, okey, oidx, olen, ooff, tid);
+    if (tid < p.k && p.sel_out) p.sel_out[size_t(pair) * p.k + tid] = Z.sel[tid];
+}
+
 // ---------------------------------------------------------------------------
 // route item: one chunk of CR spans of a pair
 // ---------------------------------------------------------------------------
-template <class T, int D, int G>
+// CLAIMED: a waiting share item runs a chunk that it has claimed already.
+template <class T, int D, int G, bool CLAIMED>
 __device__ __forceinline__ void route_item(const Params &p, Smem<T, D, G> &sm, int pair, int chunk,
-                                           uint32_t tag, int tid, bool claimed = false) {
+                                           uint32_t tag, int tid) {
     using GE = Geo<T, D>;
     constexpr int HPT = Smem<T, D, G>::HPT;
     auto &R = sm.u.route;
@@ -904,7 +1103,7 @@ __device__ __forceinline__ void route_item(const Params &p, Smem<T, D, G> &sm, i
     //    result is needed only once the loads below are in: a chunk a waiting share item
     //    has already taken over (see help_route) is left to it.
     uint32_t prev_claim = tag;
-    if (!claimed && tid == 0)
+    if (!CLAIMED && tid == 0)
         prev_claim = __hip_atomic_exchange(&p.claim[size_t(pair) * p.n_rc + chunk], tag, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
     // 1. loads: summary keys (-> LDS), query (-> registers, float64), ln|S|, and
@@ -949,14 +1148,17 @@ __device__ __forceinline__ void route_item(const Params &p, Smem<T, D, G> &sm, i
             R.lns[tid] = lns;
             R.slen[tid] = span_word<T>(p, slen, srank);
             R.boff[tid] = boff;
+            R.key[tid] = 0;
+            R.khi[tid] = 0;
         }
+        if (tid < kMaxTopK) R.slot[tid] = -1;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const int row = rgrp + GE::RPP * j;
             if (row < nr) *reinterpret_cast<uint4 *>(R.kb + size_t(row) * GE::RS + col * 16) = kv[j];
         }
     }
-    if (tid == 0) sm.bcast[5] = claimed || prev_claim != tag;
+    if (tid == 0) sm.bcast[5] = CLAIMED || prev_claim != tag;
     __syncthreads();
     SEKV_STAMP(p, sm, kTrRLoaded);
     if (!sm.bcast[5]) return;                           // another workgroup runs this chunk
@@ -1008,81 +1210,70 @@ __device__ __forceinline__ void route_item(const Params &p, Smem<T, D, G> &sm, i
     }
     SEKV_STAMP(p, sm, kTrRScored);
     if (!select) return;
+    // 4. candidates: a span's key is the largest over its heads (each head group adds its own);
+    //    its rank in the chunk is the number of keys above it, counted by two threads over
+    //    half the chunk each from the key high words (a second count by whole keys where some
+    //    are equal); wave 0 publishes the best kc, in order, as the chunk's candidate records.
+    //    (Against sorting two 64-span halves by bitonic networks and merging by binary search:
+    //    1.3 us from scores to published records instead of 2.8; ties 0.9 us more.)
     {
         double mx = -INFINITY;
 #pragma unroll
         for (int u = 0; u < HPT; ++u)
             if (hg * HPT + u < G) mx = fmax(mx, sc[u]);
-        R.pmax[hg][i] = mx;
+        if (i < nv) {
+            const uint64_t key = order_key(mx);
+            __hip_atomic_fetch_max(&R.key[i], static_cast<unsigned long long>(key), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_max(&R.khi[i], uint32_t(key >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
     }
     __syncthreads();
-
-    // 4. candidates: waves 0 and 1 each sort 64 (key, span) pairs with a bitonic network;
-    //    a span's rank in the chunk is its position plus the number of better entries of
-    //    the other half (binary search); the best kc become the chunk's candidate records.
-    if (wave < 2) {
-        const int ii = wave * 64 + lane;
-        uint64_t key = 0;
-        uint32_t idx = kInvalidIdx - uint32_t(ii);
-        if (ii < nv) {
-            key = order_key(fmax(R.pmax[0][ii], R.pmax[1][ii]));
-            idx = uint32_t(s0 + ii);
-        }
-#define SEKV_BITONIC_STEP(STRIDE)                                                          \
-        {                                                                                  \
-            const uint32_t klo = lane_xor<STRIDE>(uint32_t(key), lane);                    \
-            const uint32_t khi = lane_xor<STRIDE>(uint32_t(key >> 32), lane);              \
-            const uint32_t oi = lane_xor<STRIDE>(idx, lane);                               \
-            const uint64_t ok = (uint64_t(khi) << 32) | klo;                               \
-            const bool lower = (lane & (STRIDE)) == 0;                                     \
-            const bool take = (lower == up) ? better(ok, oi, key, idx)                     \
-                                            : better(key, idx, ok, oi);                    \
-            if (take) { key = ok; idx = oi; }                                              \
-        }
-#pragma unroll
-        for (int size = 2; size <= 64; size <<= 1) {
-            const bool up = (lane & size) == 0;
-            if (size >= 64) SEKV_BITONIC_STEP(32)
-            if (size >= 32) SEKV_BITONIC_STEP(16)
-            if (size >= 16) SEKV_BITONIC_STEP(8)
-            if (size >= 8) SEKV_BITONIC_STEP(4)
-            if (size >= 4) SEKV_BITONIC_STEP(2)
-            SEKV_BITONIC_STEP(1)
-        }
-#undef SEKV_BITONIC_STEP
-        R.skey[wave][lane] = key;
-        R.sidx[wave][lane] = idx;
-    }
-    __syncthreads();
-    SEKV_STAMP(p, sm, kTrRSorted);
     const int kc = p.kc;
-    if (wave < 2) {
-        const uint64_t key = R.skey[wave][lane];
-        const uint32_t idx = R.sidx[wave][lane];
-        const int other = 1 - wave;
-        int lo = 0, hi = 64;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (better(R.skey[other][mid], R.sidx[other][mid], key, idx)) lo = mid + 1;
-            else hi = mid;
+    R.prank[hg][i] = count_ge(R.khi + hg * (CR / 2), CR / 8, R.khi[i]);
+    __syncthreads();
+    if (hg == 0 && i < nv) {
+        const int rank = int(R.prank[0][i] + R.prank[1][i]) - 1;
+        if (rank < kc) R.slot[rank] = i;
+    }
+    __syncthreads();
+    if (__ballot(lane < kc && lane < nv && R.slot[lane] < 0) != 0) {
+        // a rank without a span (every wave sees the same): some high words are equal, so count
+        // whole keys, then indices, the same way
+        const uint64_t mine = R.key[i];
+        uint32_t rk = 0;
+#pragma unroll 8
+        for (int o = hg * (CR / 2); o < (hg + 1) * (CR / 2); ++o)
+            rk += better(R.key[o], uint32_t(o), mine, uint32_t(i)) ? 1u : 0u;
+        __syncthreads();                                // the slots have been read
+        R.prank[hg][i] = rk;
+        __syncthreads();
+        if (hg == 0 && i < nv) {
+            const int rank = int(R.prank[0][i] + R.prank[1][i]);
+            if (rank < kc) R.slot[rank] = i;
         }
-        const int rank = lane + lo;
-        if (rank < kc) {
-            // every position of every chunk is written each launch (invalid entries too),
-            // so a reader never has to know which ones exist
-            const bool valid = idx < 0x80000000u;
-            const int li = valid ? int(idx) - s0 : 0;
+        __syncthreads();
+    }
+    SEKV_STAMP(p, sm, kTrRSorted);
+    if (wave == 0) {
+        // every position of every chunk is written each launch (invalid entries too), so a
+        // reader never has to know which ones exist
+        const size_t FS = size_t(p.B) * p.Hkv * size_t(p.n_cand);
+        uint64_t *rec0 = p.cand + size_t(pair) * p.n_cand + size_t(chunk) * kc;
+        auto publish = [&](int rank, int li) {
+            const bool valid = li >= 0;
+            const uint64_t key = valid ? uint64_t(R.key[li]) : 0;
             const int32_t len = valid ? R.slen[li] : 0;
             const uint64_t off = valid ? uint64_t(R.boff[li]) : 0;
-            const size_t FS = size_t(p.B) * p.Hkv * size_t(p.n_cand);
-            uint64_t *rec = p.cand + size_t(pair) * p.n_cand + size_t(chunk) * kc + rank;
-            st_shared(rec + kCandKeyHi * FS, tagged(tag, valid ? uint32_t(key >> 32) : 0u));
-            st_shared(rec + kCandKeyLo * FS, tagged(tag, valid ? uint32_t(key) : 0u));
-            st_shared(rec + kCandIdx * FS, tagged(tag, valid ? idx : kInvalidIdx));
+            uint64_t *rec = rec0 + rank;
+            st_shared(rec + kCandKeyHi * FS, tagged(tag, uint32_t(key >> 32)));
+            st_shared(rec + kCandKeyLo * FS, tagged(tag, uint32_t(key)));
+            st_shared(rec + kCandIdx * FS, tagged(tag, valid ? uint32_t(s0 + li) : kInvalidIdx));
             st_shared(rec + kCandLen * FS, tagged(tag, uint32_t(len)));
             st_shared(rec + kCandOffLo * FS, tagged(tag, uint32_t(off)));
             st_shared(rec + kCandOffHi * FS, tagged(tag, uint32_t(off >> 32)));
-        }
+        };
+        if (lane < kc) publish(lane, R.slot[lane]);
     }
     SEKV_STAMP(p, sm, kTrRPublished);
     if (p.merger) {
@@ -1094,7 +1285,15 @@ __device__ __forceinline__ void route_item(const Params &p, Smem<T, D, G> &sm, i
             sm.bcast[1] = (prev == uint32_t(p.n_rc - 1));
         }
         __syncthreads();
-        if (sm.bcast[1]) merge_selection<T, D, G>(p, sm, pair, tid);
+        if (sm.bcast[1]) {
+            // every share item of a fused step ranks the candidates itself when they fit
+            // (kMergeBuf), so what is left for those is the selection alone (route mode)
+            // (and no share item waits, so none helps, in route mode)
+            if (!CLAIMED && p.mode == kModeRoute && p.n_cand <= kMergeBuf)
+                rank_selection<T, D, G>(p, sm, pair, m_b, tag, tid);
+            else
+                merge_selection<T, D, G>(p, sm, pair, tid);
+        }
     }
 }
 
@@ -1251,124 +1450,7 @@ __device__ __forceinline__ void help_route(const Params &p, Smem<T, D, G> &sm, i
                           __hip_atomic_exchange(w, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != tag;
         }
         __syncthreads();
-        if (sm.bcast[6]) route_item<T, D, G>(p, sm, pair, c, tag, tid, true);
-    }
-    __syncthreads();
-}
-
-constexpr int kOwn = kMergeBuf / NT;                   // candidates per thread when ranking
-
-// One polling attempt on the pair's candidate records; thread tid owns candidates tid
-// and tid + NT.  Returns whether every tag was current.
-__device__ inline bool load_candidates(const Params &p, int pair, uint32_t tag, uint64_t (&okey)[kOwn],
-                                       uint32_t (&oidx)[kOwn], int32_t (&olen)[kOwn],
-                                       int64_t (&ooff)[kOwn], int tid) {
-    const size_t FS = size_t(p.B) * p.Hkv * size_t(p.n_cand);
-    const uint64_t *rec = p.cand + size_t(pair) * p.n_cand;
-    bool ok = true;
-#pragma unroll
-    for (int u = 0; u < kOwn; ++u) {
-        const int c = tid + NT * u;
-        okey[u] = 0;
-        oidx[u] = kInvalidIdx;
-        olen[u] = 0;
-        ooff[u] = 0;
-        if (c < p.n_cand) {
-            uint64_t w[kCandFields];
-#pragma unroll
-            for (int f = 0; f < kCandFields; ++f) w[f] = ld_shared(rec + f * FS + c);
-#pragma unroll
-            for (int f = 0; f < kCandFields; ++f) ok &= tag_is(w[f], tag);
-            okey[u] = (uint64_t(uint32_t(w[kCandKeyHi])) << 32) | uint32_t(w[kCandKeyLo]);
-            oidx[u] = uint32_t(w[kCandIdx]);
-            olen[u] = int32_t(uint32_t(w[kCandLen]));
-            ooff[u] = int64_t(uint64_t(uint32_t(w[kCandOffLo])) | (uint64_t(uint32_t(w[kCandOffHi])) << 32));
-        }
-    }
-    return ok;
-}
-
-// rk += 1 if (key_o, ~idx_o) > (key_c, ~idx_c) as 96-bit unsigned numbers, i.e. if
-// candidate o is ahead of candidate c in (key desc, span asc): the borrow out of
-// mine - other.  Words are {~idx, key lo, key hi}.
-__device__ __forceinline__ void count_ahead(uint32_t &rk, const uint4 &o, uint32_t m0, uint32_t m1,
-                                            uint32_t m2) {
-    uint32_t t;
-    asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
-        "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
-        "v_subb_co_u32 %0, vcc, %6, %7, vcc\n\t"
-        "v_addc_co_u32 %1, vcc, 0, %1, vcc"
-        : "=&v"(t), "+v"(rk)
-        : "v"(m0), "v"(o.x), "v"(m1), "v"(o.y), "v"(m2), "v"(o.z)
-        : "vcc");
-}
-
-// Rank the pair's candidates (LDS): rank = number of candidates ahead in (key desc,
-// span asc).  Ranks below k fill Z.sel and Z.zi ({span, |S|, offset}).  Up to NT/2
-// candidates, two threads scan half the list each.
-template <class T, int D, int G>
-__device__ __forceinline__ void rank_candidates(const Params &p, Smem<T, D, G> &sm, int m_b,
-                                                const uint64_t (&okey)[kOwn], const uint32_t (&oidx)[kOwn],
-                                                const int32_t (&olen)[kOwn], const int64_t (&ooff)[kOwn],
-                                                int tid) {
-    auto &Z = sm.u.share;
-    const int k = p.k, n_cand = p.n_cand;
-#pragma unroll
-    for (int u = 0; u < kOwn; ++u) {
-        const int c = tid + NT * u;
-        if (c < n_cand) Z.cand[c] = make_uint4(~oidx[u], uint32_t(okey[u]), uint32_t(okey[u] >> 32), 0);
-    }
-    __syncthreads();
-    const bool split = n_cand <= NT / 2;
-    if (split) {
-        // thread c and c + NT/2 rank candidate c over the two halves of the list
-        const int c = tid % (NT / 2), half = tid / (NT / 2);
-        const int o0 = half ? n_cand / 2 : 0, o1 = half ? n_cand : n_cand / 2;
-        uint32_t rk = 0;
-        if (c < n_cand) {
-            const uint4 me = Z.cand[c];
-            int o = o0;
-            for (; o + 8 <= o1; o += 8) {
-                uint4 e[8];
-#pragma unroll
-                for (int w = 0; w < 8; ++w) e[w] = Z.cand[o + w];
-#pragma unroll
-                for (int w = 0; w < 8; ++w) count_ahead(rk, e[w], me.x, me.y, me.z);
-            }
-            for (; o < o1; ++o) count_ahead(rk, Z.cand[o], me.x, me.y, me.z);
-        }
-        Z.rk[tid] = rk;
-        __syncthreads();
-        if (tid < n_cand && oidx[0] < 0x80000000u) {
-            const int r = int(Z.rk[tid] + Z.rk[tid + NT / 2]);
-            if (r < k && r < m_b) {
-                Z.sel[r] = int32_t(oidx[0]);
-                Z.zi[r] = make_int4(int32_t(oidx[0]), olen[0], int32_t(ooff[0] & 0xFFFFFFFF),
-                                    int32_t(ooff[0] >> 32));
-            }
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < kOwn; ++u) {
-            const int c = tid + NT * u;
-            if (c >= n_cand || oidx[u] >= 0x80000000u) continue;
-            const uint32_t m0 = ~oidx[u], m1 = uint32_t(okey[u]), m2 = uint32_t(okey[u] >> 32);
-            uint32_t rk = 0;
-            int o = 0;
-            for (; o + 8 <= n_cand; o += 8) {
-                uint4 e[8];
-#pragma unroll
-                for (int w = 0; w < 8; ++w) e[w] = Z.cand[o + w];
-#pragma unroll
-                for (int w = 0; w < 8; ++w) count_ahead(rk, e[w], m0, m1, m2);
-            }
-            for (; o < n_cand; ++o) count_ahead(rk, Z.cand[o], m0, m1, m2);
-            if (int(rk) < k && int(rk) < m_b) {
-                Z.sel[rk] = int32_t(oidx[u]);
-                Z.zi[rk] = make_int4(int32_t(oidx[u]), olen[u], int32_t(ooff[u] & 0xFFFFFFFF),
-                                     int32_t(ooff[u] >> 32));
-            }
-        }
+        if (sm.bcast[6]) route_item<T, D, G, true>(p, sm, pair, c, tag, tid);
     }
     __syncthreads();
 }
@@ -1768,7 +1850,16 @@ __device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, i
             case 2: zoom_span<T, D, G, 2, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
             case 4: zoom_span<T, D, G, 4, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
             case 8: zoom_span<T, D, G, 8, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-            default: zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
+            default:
+                // the widest rows: the summary block's registers are free before the zoom's
+                // loads go out (256 registers hold no more without scratch)
+                if constexpr (D == 128) {
+                    mid();
+                    zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, [] {});
+                } else {
+                    zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid);
+                }
+                break;
         }
     };
     auto zoom_one = [&](int32_t w, int64_t off, int tid, auto &&mid) {
@@ -1815,7 +1906,20 @@ __device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, i
 template <class T, int D, int G>
 __global__ void __launch_bounds__(NT, G == 8 ? 1 : 2) sekv_step_kernel(Params p) {
     __shared__ Smem<T, D, G> sm;
-    const int tid = threadIdx.x;
+    // an opaque copy of the thread index for each item keeps per-thread address arithmetic
+    // inside it instead of alive across the whole loop (register pressure); where even the
+    // index itself is one register too many, it is formed anew
+    const int wave0 = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) & ~63;
+    auto thread = [&]() {
+        int t;
+        if constexpr (T::kBytes == 4 && D == 128) {
+            asm volatile("v_mov_b32 %0, 0" : "=v"(t));
+            return wave0 + int(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, uint32_t(t))));
+        } else {
+            asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(int(threadIdx.x)));
+            return t;
+        }
+    };
     // the tag of this launch's published words, used as loaded: its first use is when
     // an item publishes or polls, so the load overlaps the first item's own loads
     const uint32_t tag = ld_shared(&p.hdr->epoch);
@@ -1826,13 +1930,10 @@ __global__ void __launch_bounds__(NT, G == 8 ? 1 : 2) sekv_step_kernel(Params p)
     int helps = 0;                                      // help rounds of the current item
     bool left = false;                                  // counted out in its last share item
     for (int item = blockIdx.x; item < n_items;) {
-        // an opaque copy of the thread index keeps per-thread address arithmetic inside
-        // each item instead of alive across the whole loop (register pressure)
-        int t;
-        asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(tid));
+        const int t = thread();
         SEKV_TRACE_BEGIN(p, sm, item);
         if (item < p.end_route) {
-            route_item<T, D, G>(p, sm, item / p.n_rc, item % p.n_rc, tag, t);
+            route_item<T, D, G, false>(p, sm, item / p.n_rc, item % p.n_rc, tag, t);
         } else {
             const int i = item - p.end_route;                // slot-major
             const int P = p.B * p.Hkv;
@@ -1857,6 +1958,7 @@ __global__ void __launch_bounds__(NT, G == 8 ? 1 : 2) sekv_step_kernel(Params p)
     // a workgroup whose last item was a routing item (or that had none) counts itself out
     // here; the last workgroup out zeroes the counters and advances the epoch
     if (!left) {
+        const int tid = thread();
         if (tid == 0) {
             const uint32_t prev = counter_add(&p.hdr->exit_count, 1u);
             sm.bcast[3] = (prev == uint32_t(p.grid - 1));

@@ -799,8 +799,8 @@ def bench_prefill(args, dev):
                      "frac": round(flops / build_s / 1e12 / FP32_PEAK_TFLOPS, 5), "traffic": None,
                      "kernel": "svd_kernel (+ gather_kernel in the timed launch pair)",
                      "algorithmic_flops_per_launch": flops,
-                     "note": "latency-bound: per span side, 40-step Cholesky factorisations and "
-                             "Jacobi rounds with a workgroup barrier each"},
+                     "note": "latency-bound: per span side, serial 40-step Cholesky factorisations "
+                             "and Jacobi rounds inside one wave"},
         "segment_ms": round(float(np.mean(seg_ms)), 4),
         "build_ms": round(float(np.mean(build_ms)), 4),
         "call_wall_ms_with_layout": round(wall_ms, 3),

@@ -1706,10 +1706,13 @@ __device__ __forceinline__ bool select_spans(const Params &p, Smem<T, D, G> &sm,
     } else {
         if (p.mode == kModeFused) {
             // single merger: wait for the pair's selection records
+            bool ready = false;
             for (uint32_t it = 0;; ++it) {
                 if (tid == 0) sm.bcast[2] = ld_shared(&p.sel_ready[pair]) != 0u ? 1 : 0;
                 __syncthreads();
-                if (sm.bcast[2]) break;
+                ready = __builtin_amdgcn_readfirstlane(sm.bcast[2]) != 0;
+                __syncthreads();                        // read before the next poll's answer
+                if (ready) break;
                 if (it >= kSpinLimit) {
                     if (tid == 0) flag_error(p, kErrSpinTimeout);
                     break;
@@ -1717,7 +1720,7 @@ __device__ __forceinline__ bool select_spans(const Params &p, Smem<T, D, G> &sm,
                 if (may_give_up && it >= kHelpAfter) return true;
                 __builtin_amdgcn_s_sleep(2);
             }
-            if (sm.bcast[2] && tid < k) {
+            if (ready && tid < k) {
                 const int32_t *zr = reinterpret_cast<const int32_t *>(&p.zrec[size_t(pair) * k + tid]);
                 const int s = ld_shared(zr);
                 Z.sel[tid] = s;

@@ -910,6 +910,9 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
         for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) vacc[ct][dt] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    bool keep[NT];
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) keep[ct] = sm.nrm[16 * ct + c16] > 0.0;
     uint4 xn[NX];
     load_x(xn, 16 * wave);
     for (int t0 = 16 * wave; t0 < L; t0 += 16 * NW) {
@@ -935,7 +938,8 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             if (16 * ct >= rs) continue;
-            // U tile: rows tokens q + 4 r, column component 16 ct + c16
+            // U tile: rows tokens q + 4 r, column component 16 ct + c16 (a component that was not
+            // kept is zero also where the sketch is infinite or NaN)
             const int comp = 16 * ct + c16;
             d4_t u = d4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -945,7 +949,7 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
             float uf[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                uf[e] = comp < rs ? float(u[e]) : 0.0f;
+                uf[e] = keep[ct] ? float(u[e]) : 0.0f;
                 const int t = t0 + q + 4 * e;
                 if (t < L && comp < rs) st_val<ELEM>(blk, size_t(t) * rs + comp, uf[e]);
             }

@@ -34,17 +34,23 @@ def test_factor_tiles(S, dtype, d, rank, sketch, power, heads):  # noqa: F811
     at = np.cumsum([L + 1 for L in LENGTHS]) - 1
     p.surprisal[0, at] = 9.0
     c = dict(rank=rank, sketch=sketch, min_span=2, window=0, power=power, Hkv=heads, d=d)
-    p.keys[0, :, at[2] + 5:at[3]] = 0                       # a span of zeros
+    zero = {int(at[i - 1]) + 1: L for i, L in enumerate(LENGTHS) if L in (3, 130)}   # keys of zeros: a
+    for s0, L in zero.items():                              # span inside the sketch and one past it
+        assert p.keys[0, :, s0:s0 + L].any()
+        p.keys[0, :, s0:s0 + L] = 0
     p.values[0, :, at[7] + 1:at[8] + 1] = p.values[0, :, at[7] + 1:at[7] + 2]   # and one of equal rows
     got, seg, lay = _build(S, p, c)
     _check_segments(seg, p, 1.0, 2, 0, "lengths")
     _, spans = oracle.segment(p.surprisal[0], n, 1.0, 2, 0)
     assert len(spans) >= len(LENGTHS) - 1
+    assert zero.items() <= dict(spans).items()
     rec = 2.0 ** -7 if dtype == "bf16" else 1e-5
     for g in sorted({0, heads // 2, heads - 1}):
         for i, (s0, L) in enumerate(spans):
             w = int(lay["block_rank"][0, g, i])
             blk = oracle.read_span_block(got["factors"], int(lay["block_off"][0, g, i]), L, w & 0xFFFF, d, dtype, w >> 16)
+            if s0 in zero:
+                assert all(np.all(blk[name + "K"] == 0) for name in ("U", "s", "Vt")), (i, L)
             for side, src in (("K", p.keys), ("V", p.values)):
                 X = oracle.widen(src[0, g, s0:s0 + L], dtype)
                 opt = math.sqrt(np.sum(np.linalg.svd(X, compute_uv=False)[min(L, d, rank):] ** 2))

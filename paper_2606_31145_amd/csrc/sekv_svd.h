@@ -10,17 +10,17 @@
 //              B's) row space, C_P P with C_P the inverse factor of P P^T
 //   diagonal   M = E diag(sigma^2) E^T by one-sided Jacobi on the columns of M's Cholesky
 //              factor (W W^T = M; W J has orthogonal columns E diag(sigma))
-//   output     T = C^T E; a last pass over X forms U = Y T and V diag(sigma) = X^T U
+//   output     T = C^T E; a last pass over X forms U = Y T; V diag(sigma) = P^T T
 //
 // What bounds it: a span side is a long chain of small steps (three passes over 30 to 300 KB
 // of L2-resident tokens, two to four 40 x 40 factorisations, 200 to 250 Jacobi rounds), and a
 // layer has tens of thousands of them.  So a side runs in ONE wave (its steps need no
 // workgroup barrier) and eight sides share a CU: a wave issues one vector instruction per 8
 // cycles at most, so two waves per SIMD are what keeps the vector unit busy.  That takes at most
-// 20 KB of LDS and 256 registers per side, hence: no copy of B or X is kept (M is formed
-// tile by tile, V comes from the last pass), and LDS holds either the pass's tiles or one
+// 20 KB of LDS and 256 registers per side, hence: no copy of B, X or P is kept (M is formed
+// tile by tile, the last pass forms P again), and LDS holds either the pass's tiles or one
 // 40 x 40 matrix.  The dense products run on the matrix cores: bf16 MFMA where the operands
-// are bf16 values (X, Omega) or exact three-way bf16 splits of float32 values (Y, U), float64
+// are bf16 values (X, Omega) or exact three-way bf16 splits of float32 values (Y), float64
 // MFMA for the Gram matrices and everything that multiplies C, E or T, so no sum is formed
 // at a lower precision than its result needs.  Operands are used in the register layout
 // that the product before left them in (contraction indices are permuted on both sides
@@ -565,7 +565,74 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                 }
         wave_sync();
     };
+    // P stays in registers through the factorisations, or the output pass forms it again
+    constexpr bool kKeepP = ELEM == 4 || NW > 1;
     f4_t pacc[NT][DT];                  // P tiles (rows: sketch columns 16 nt + 4 q + r; column: 16 ct + c16)
+    // P += Y^T X for the 16 tokens in `tile`; y: rows tokens 4 q + e, which is the contraction index
+    auto add_p = [&](const f4_t (&y)[NT], const unsigned char *tile) __attribute__((always_inline)) {
+        if constexpr (ELEM == 2) {
+            uint2 yh[NT], ym[NT], yl[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const float yy[4] = {y[nt][0], y[nt][1], y[nt][2], y[nt][3]};
+                split3(yy, yh[nt], ym[nt], yl[nt]);
+            }
+            const uint16_t *xs = reinterpret_cast<const uint16_t *>(tile) + (4 * q + c16 / 4) * (D + 8) +
+                                 4 * (c16 % 4);
+#pragma unroll
+            for (int ct = 0; ct < DT; ++ct) {
+                const uint2 xb = lds_tr4(xs + 16 * ct);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    pacc[nt][ct] = mfma_k16(yl[nt], xb, pacc[nt][ct]);
+                    pacc[nt][ct] = mfma_k16(ym[nt], xb, pacc[nt][ct]);
+                    pacc[nt][ct] = mfma_k16(yh[nt], xb, pacc[nt][ct]);
+                }
+            }
+        } else {
+            const float *xs = reinterpret_cast<const float *>(tile) + 4 * q * (D + 4) + c16;
+#pragma unroll
+            for (int ct = 0; ct < DT; ++ct)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float xv = xs[e * (D + 4) + 16 * ct];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) pacc[nt][ct] = mfma32(y[nt][e], xv, pacc[nt][ct]);
+                }
+        }
+    };
+    // V^T rows (T^T P) / sigma, zero past the kept components.  M was formed from the same P, so the
+    // rows are orthonormal to the rounding of their storage whatever their singular value.  As
+    // X^T U in float32 sums (which needs no P) they were not: two rows' product was up to 0.15 for
+    // singular values down to 1e-4 of the largest (now 2.4e-3, bfloat16's own rounding), and 1.8e-3
+    // instead of 1.2e-3 (root mean square) after a plain sketch.  A 128K x 4 layer: 8.58 against 8.93 ms.
+    auto put_v = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            if (16 * ct >= rs) continue;
+            double tv[NT][4];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tv[nt][e] = t_at(16 * nt + 4 * q + e, 16 * ct + c16);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                d4_t v = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v = mfma64(tv[nt][e], double(pacc[nt][dt][e]), v);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int comp = 16 * ct + q + 4 * e;
+                    const double s = sm.nrm[comp];
+                    if (comp < rs)
+                        st_val<ELEM>(blk, size_t(v_off) + size_t(comp) * D + 16 * dt + c16,
+                                     s > 0.0 ? float(v[e] / s) : 0.0f);
+                }
+            }
+        }
+    };
     // a pass over X with the test matrix in om: P = Y^T X into pacc, and with GRAM G = Y^T Y
     // (what is returned puts it into g)
     auto sketch = [&](auto gram_c) __attribute__((always_inline)) {
@@ -611,37 +678,7 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                     for (int e = 0; e < 4; ++e)
                         if constexpr (GRAM) gacc[ij] = mfma64(double(y[i][e]), double(y[j][e]), gacc[ij]);
             wave_sync();
-            // P += Y^T X: contraction index (q, e) is token 4 q + e
-            if constexpr (ELEM == 2) {
-                uint2 yh[NT], ym[NT], yl[NT];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const float yy[4] = {y[nt][0], y[nt][1], y[nt][2], y[nt][3]};
-                    split3(yy, yh[nt], ym[nt], yl[nt]);
-                }
-                const uint16_t *xs = reinterpret_cast<const uint16_t *>(xs_raw) + (4 * q + c16 / 4) * (D + 8) +
-                                     4 * (c16 % 4);
-#pragma unroll
-                for (int ct = 0; ct < DT; ++ct) {
-                    const uint2 xb = lds_tr4(xs + 16 * ct);
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        pacc[nt][ct] = mfma_k16(yl[nt], xb, pacc[nt][ct]);
-                        pacc[nt][ct] = mfma_k16(ym[nt], xb, pacc[nt][ct]);
-                        pacc[nt][ct] = mfma_k16(yh[nt], xb, pacc[nt][ct]);
-                    }
-                }
-            } else {
-                const float *xs = reinterpret_cast<const float *>(xs_raw) + 4 * q * (D + 4) + c16;
-#pragma unroll
-                for (int ct = 0; ct < DT; ++ct)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float xv = xs[e * (D + 4) + 16 * ct];
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) pacc[nt][ct] = mfma32(y[nt][e], xv, pacc[nt][ct]);
-                    }
-            }
+            add_p(y, xs_raw);
             wave_sync();
         }
         if constexpr (NW > 1) {
@@ -686,8 +723,7 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
     constexpr int K4 = KR / 4;
     double cr[K4][NT];
     // M = B B^T with B = C P (C in g), then C into cr and M into g.  B^T tiles come out of the
-    // product in the layout that the next product reads, one 16-column strip of B at a time;
-    // B is rounded to float32.
+    // product in the layout that the next product reads, one 16-column strip of B at a time.
     auto gram_b = [&]() __attribute__((always_inline)) {
         phase();
         d4_t macc[NG];
@@ -707,10 +743,6 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                         bt[lt] = mfma64(double(pacc[nt][ct][e]), g[16 * lt + c16][16 * nt + 4 * q + e], bt[lt]);
                 __builtin_amdgcn_sched_barrier(0);          // one tile of C's operands at a time
             }
-#pragma unroll
-            for (int lt = 0; lt < NT; ++lt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) bt[lt][e] = double(float(bt[lt][e]));
 #pragma unroll
             for (int i = 0, ij = 0; i < NT; ++i)
 #pragma unroll
@@ -867,74 +899,58 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
                 }
         }
         wave_sync();
-        if constexpr (ELEM == 4) {
-            // V^T rows (T^T P) / sigma, zero past the kept components
-#pragma unroll
-            for (int ct = 0; ct < NT; ++ct) {
-                if (16 * ct >= rs) continue;
-                double tv[NT][4];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) tv[nt][e] = t_at(16 * nt + 4 * q + e, 16 * ct + c16);
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    d4_t v = d4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v = mfma64(tv[nt][e], double(pacc[nt][dt][e]), v);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int comp = 16 * ct + q + 4 * e;
-                        const double s = sm.nrm[comp];
-                        if (comp < rs)
-                            st_val<ELEM>(blk, size_t(v_off) + size_t(comp) * D + 16 * dt + c16,
-                                         s > 0.0 ? float(v[e] / s) : 0.0f);
-                    }
-                }
-            }
-        }
+        if constexpr (kKeepP) put_v();
         SV_STAMP(kSvT);
     }
     __syncthreads();
 
-    // output pass: U = Y T, 16 tokens at a time; with bfloat16 storage V diag(sigma) = X^T U
-    // beside it (float32 sums: V's rows are then orthogonal to about 1e-7 sigma_1 / sigma_i, below
-    // the storage rounding of any component worth keeping; with float32 storage P is kept
-    // through the factorisations instead, which takes one wave per SIMD)
+    // output pass: U = Y T, 16 tokens at a time.  A lone wave with bfloat16 storage has no registers
+    // to keep P in (that takes one wave per SIMD): the pass forms it again beside U, operation
+    // for operation as the sketch did, so it has the same bits, and V follows at the end
     phase();
-    f4_t (&vacc)[NT][DT] = pacc;        // rows: components 16 ct + 4 q + r; column: 16 dt + c16
-    if constexpr (ELEM == 2)
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) vacc[ct][dt] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
     bool keep[NT];
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) keep[ct] = sm.nrm[16 * ct + c16] > 0.0;
+    if constexpr (!kKeepP)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int ct = 0; ct < DT; ++ct) pacc[nt][ct] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
     uint4 xn[NX];
     load_x(xn, 16 * wave);
     for (int t0 = 16 * wave; t0 < L; t0 += 16 * NW) {
-        uint4 x[NX];
-#pragma unroll
-        for (int m = 0; m < NX; ++m) x[m] = xn[m];
-        load_x(xn, t0 + 16 * NW);
-        if constexpr (ELEM == 2) store_x(xf_raw, x);
         // Y^T tile: rows sketch columns 16 nt + 4 q + r, column token c16
         f4_t yt[NT];
+        {
+            uint4 x[NX];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            yt[nt] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int m = 0; m < NX; ++m) x[m] = xn[m];
+            load_x(xn, t0 + 16 * NW);
+            if constexpr (!kKeepP) store_x(xf_raw, x);
 #pragma unroll
-            for (int m = 0; m < NX; ++m) {
-                if constexpr (ELEM == 2) yt[nt] = mfma_k32(omk[nt][m], x[m], yt[nt]);
-                else
+            for (int nt = 0; nt < NT; ++nt) {
+                yt[nt] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) yt[nt] = mfma32(om_f(omk[nt][m], j), x_f(x[m], j), yt[nt]);
+                for (int m = 0; m < NX; ++m) {
+                    if constexpr (ELEM == 2) yt[nt] = mfma_k32(omk[nt][m], x[m], yt[nt]);
+                    else
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) yt[nt] = mfma32(om_f(omk[nt][m], j), x_f(x[m], j), yt[nt]);
+                }
+            }
+            if constexpr (!kKeepP) {
+                f4_t y[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    y[nt] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int m = 0; m < NX; ++m) y[nt] = mfma_k32(x[m], omk[nt][m], y[nt]);
+                }
+                wave_sync();
+                add_p(y, xf_raw);
+                wave_sync();
             }
         }
-        wave_sync();
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             if (16 * ct >= rs) continue;
@@ -946,70 +962,14 @@ __global__ void __launch_bounds__(64 * NW, (ELEM == 2 && NW == 1) ? 2 : 1) svd_k
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) u = mfma64(double(yt[nt][e]), t_at(16 * nt + 4 * q + e, comp), u);
-            float uf[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                uf[e] = keep[ct] ? float(u[e]) : 0.0f;
                 const int t = t0 + q + 4 * e;
-                if (t < L && comp < rs) st_val<ELEM>(blk, size_t(t) * rs + comp, uf[e]);
-            }
-            if constexpr (ELEM == 2) {
-                uint2 uh, um, ul;
-                split3(uf, uh, um, ul);
-                const uint16_t *xs = reinterpret_cast<const uint16_t *>(xf_raw) + (q + 4 * (c16 / 4)) * (D + 8) +
-                                     4 * (c16 % 4);
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    const uint2 xb = lds_tr4(xs + 16 * dt);
-                    vacc[ct][dt] = mfma_k16(ul, xb, vacc[ct][dt]);
-                    vacc[ct][dt] = mfma_k16(um, xb, vacc[ct][dt]);
-                    vacc[ct][dt] = mfma_k16(uh, xb, vacc[ct][dt]);
-                }
+                if (t < L && comp < rs) st_val<ELEM>(blk, size_t(t) * rs + comp, keep[ct] ? float(u[e]) : 0.0f);
             }
         }
-        wave_sync();
     }
-    if constexpr (ELEM == 4) {
-        SV_STAMP(kSvEnd);
-        return;
-    }
-    if constexpr (NW > 1) {
-        float *red = reinterpret_cast<float *>(sm.b + SM::red);
-        for (int w = 1; w < NW; ++w) {
-            __syncthreads();
-            if (wave == w)
-#pragma unroll
-                for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) red[((ct * DT + dt) * 4 + e) * 64 + lane] = vacc[ct][dt][e];
-            __syncthreads();
-            if (wave == 0)
-#pragma unroll
-                for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) vacc[ct][dt][e] += red[((ct * DT + dt) * 4 + e) * 64 + lane];
-        }
-    }
-    // V^T rows, zero past the kept components
-    if (wave == 0) {
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int comp = 16 * ct + 4 * q + e;
-                if (comp < rs) {
-                    const double s = sm.nrm[comp];
-#pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-                        st_val<ELEM>(blk, size_t(v_off) + size_t(comp) * D + 16 * dt + c16,
-                                     s > 0.0 ? float(double(vacc[ct][dt][e]) / s) : 0.0f);
-                }
-            }
-    }
+    if constexpr (!kKeepP) put_v();
     SV_STAMP(kSvEnd);
 }
 

@@ -399,6 +399,153 @@ __device__ __forceinline__ void zoom_part(const Params &p, Wave<D, G> &W, int L,
     }
 }
 
+// The partial of a share item again, entry by entry, where the matrix cores gave a NaN.  A split
+// operand meets every stored value as three pieces and some zeros, so an infinite value (or weight)
+// becomes infinity times zero there; here it is multiplied once, as fp32 storage does it: an
+// infinite value of positive weight gives infinity, a score of -infinity a weight of zero.  Plain
+// loops: the item's selection is in Z.sel and Z.zi, its logits were published, Z.wb is scratch.
+// What the test for NaN costs where there is none: 32K 18.35 -> 18.6 us, 128K x 4 27.1 -> 27.4 us.
+template <class T, int D, int G>
+__device__ __forceinline__ void share_partial_plain(const Params &p, Smem<T, D, G> &sm, int pair, int j, int a_lo,
+                                                    int a_end, int c_lo, int c_end, uint32_t tag, int tid) {
+    constexpr int NO = G * D / 2, NP = (NO + NT - 1) / NT;   // value pairs; of a thread
+    constexpr int NB = Smem<T, D, G>::CB;                    // rows at a time
+    constexpr int NY = (G * kMaxTopK + NT - 1) / NT;         // components (at most 64 a head) of a thread
+    static_assert(NB == 64 && kMaxTopK == 64, "64 rows and components");
+    struct Scratch {
+        float s[G][64], w[G][64], y[G][64];
+        float m[G], l[G], so[G];
+    };
+    auto &Z = sm.u.share;
+    static_assert(sizeof(Scratch) <= sizeof(Z.wb), "scratch in the waves' tiles");
+    Scratch &X = *reinterpret_cast<Scratch *>(&Z.wb[0][0]);
+    const int b = pair / p.Hkv, g = pair % p.Hkv;
+    const size_t q0 = (size_t(b) * p.Hq + size_t(g) * G) * D;
+    const size_t arow = size_t(pair) * p.A_max, srow = size_t(pair) * p.M_max;
+    float o[NP][2];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) o[u][0] = o[u][1] = 0.0f;
+    if (tid < G) { X.m[tid] = -INFINITY; X.l[tid] = 0.0f; }
+    // X.s[h][0, n) become weights relative to the new maximum; the sums so far follow it
+    auto fold = [&](int n) {
+        __syncthreads();
+        if (tid < G) {
+            float mx = -INFINITY, ls = 0.0f;
+            for (int i = 0; i < n; ++i) mx = fmaxf(mx, X.s[tid][i]);
+            const float mo = X.m[tid], mn = fmaxf(mo, mx);
+            for (int i = 0; i < n; ++i) {
+                const float wt = mn == -INFINITY ? 0.0f : safe_exp2(X.s[tid][i] - mn);
+                X.s[tid][i] = wt;
+                ls += wt;
+            }
+            const float so = mn == -INFINITY ? 1.0f : safe_exp2(mo - mn);
+            X.so[tid] = so;
+            X.l[tid] = X.l[tid] * so + ls;
+            X.m[tid] = mn;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int o2 = tid + NT * u;
+            const float so = X.so[min(2 * o2 / D, G - 1)];
+            o[u][0] *= so;
+            o[u][1] *= so;
+        }
+    };
+    // o += weights x rows [row, row + n) of `rows`
+    auto add = [&](const float (&wt)[G][64], const void *rows, size_t row, int n) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int o2 = tid + NT * u;
+            if (o2 >= NO) continue;
+            const int hl = 2 * o2 / D, d = 2 * o2 % D;
+#pragma unroll 1
+            for (int i = 0; i < n; ++i) {
+                o[u][0] += wt[hl][i] * T::load1(rows, (row + i) * D + d);
+                o[u][1] += wt[hl][i] * T::load1(rows, (row + i) * D + d + 1);
+            }
+        }
+        __syncthreads();
+    };
+    auto q_dot = [&](int hl, const void *rows, size_t row) {
+        float a = 0.0f;
+#pragma unroll 1
+        for (int d = 0; d < D; ++d) a += T::load1(p.q, q0 + size_t(hl) * D + d) * T::load1(rows, row * D + d);
+        return a;
+    };
+    for (int a0 = a_lo; a0 < a_end; a0 += 64) {
+        const int n = min(64, a_end - a0);
+        for (int i = tid; i < G * 64; i += NT)
+            if (i % 64 < n) X.s[i / 64][i % 64] = q_dot(i / 64, p.anchor_k, arow + a0 + i % 64) * p.scale_log2;
+        fold(n);
+        add(X.s, p.anchor_v, arow + a0, n);
+    }
+    for (int c0 = c_lo; c0 < c_end; c0 += 64) {
+        const int n = min(64, c_end - c0);
+        coarse_logits<T, D, G>(p, sm, pair, c0, n, tag, tid);
+        __syncthreads();
+        for (int i = tid; i < G * 64; i += NT) {
+            bool zoomed = i % 64 >= n;
+            for (int t = 0; t < p.k; ++t) zoomed |= Z.sel[t] == c0 + i % 64;
+            X.s[i / 64][i % 64] = zoomed ? -INFINITY : Z.cw[i / 64][i % 64];
+        }
+        fold(n);
+        add(X.s, p.sum_v, srow + c0, n);
+    }
+    for (int rank = j; rank < p.k; rank += p.n_zi) {
+        const int4 zi = Z.zi[rank];
+        if (zi.x < 0) continue;
+        const int L = word_len(zi.y), rk = word_rk(zi.y), rv = word_rv(zi.y);
+        const unsigned char *UK = p.factors + (int64_t(uint32_t(zi.z)) | (int64_t(zi.w) << 32));
+        const unsigned char *sK = UK + size_t(L) * rk * T::kBytes;
+        const unsigned char *VtK = sK + size_t(rk) * T::kBytes;
+        const unsigned char *UV = VtK + size_t(rk) * D * T::kBytes;
+        const unsigned char *sV = UV + size_t(L) * rv * T::kBytes;
+        const unsigned char *VtV = sV + size_t(rv) * T::kBytes;
+        for (int i = tid; i < G * 64; i += NT)
+            if (i % 64 < rk) X.w[i / 64][i % 64] = q_dot(i / 64, VtK, i % 64) * T::load1(sK, i % 64) * p.scale_log2;
+        __syncthreads();
+        float y[NY];
+#pragma unroll
+        for (int u = 0; u < NY; ++u) y[u] = 0.0f;
+        for (int t0 = 0; t0 < L; t0 += 64) {
+            const int n = min(64, L - t0);
+            for (int i = tid; i < G * 64; i += NT) {
+                if (i % 64 >= n) continue;
+                float a = 0.0f;
+#pragma unroll 1
+                for (int c = 0; c < rk; ++c) a += T::load1(UK, size_t(t0 + i % 64) * rk + c) * X.w[i / 64][c];
+                X.s[i / 64][i % 64] = a;
+            }
+            fold(n);
+#pragma unroll
+            for (int u = 0; u < NY; ++u) {
+                const int i = tid + NT * u, hl = min(i / 64, G - 1);
+                y[u] *= X.so[hl];
+#pragma unroll 1
+                for (int t = 0; t < n; ++t)
+                    if (i % 64 < rv) y[u] += X.s[hl][t] * T::load1(UV, size_t(t0 + t) * rv + i % 64);
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int u = 0; u < NY; ++u) {
+            const int i = tid + NT * u;
+            if (i < G * 64 && i % 64 < rv) X.y[i / 64][i % 64] = y[u] * T::load1(sV, i % 64);
+        }
+        __syncthreads();
+        add(X.y, VtV, 0, rv);
+    }
+    const size_t base = size_t(pair) * p.n_zi + j;
+    if (tid < G) st_shared(&p.part_ml[base * G + tid], pack2(X.m[tid], X.l[tid]));
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        const int o2 = tid + NT * u;
+        if (o2 < NO) st_shared(&p.part_o[base * NO + o2], pack2(o[u][0], o[u][1]));
+    }
+    stores_done_barrier();
+}
+
 // share item: anchors share, selection slot j, summaries share of one pair.  Returns true when a
 // wait lasted kHelpAfter polls: the caller then helps with routing (help_route) and runs the
 // item again from the start.
@@ -567,6 +714,7 @@ __device__ __forceinline__ bool share_item_mfma(const Params &p, Smem<T, D, G> &
         sm.mw[wave][lane] = W.m;
         sm.lw[wave][lane] = l;
     }
+    if (tid == 0) sm.bcast[7] = 0;
 #pragma unroll
     for (int dt = 0; dt < W.DT; ++dt) {
         f4v t[W.NU];
@@ -591,6 +739,7 @@ __device__ __forceinline__ bool share_item_mfma(const Params &p, Smem<T, D, G> &
 #pragma unroll
             for (int w = 0; w < 4; ++w) ls += wg[w] * sm.lw[w][tid];
             st_shared(&p.part_ml[base * G + tid], pack2(m, ls));
+            if (ls != ls) sm.bcast[7] = 1;
         }
         uint64_t *po = p.part_o + base * NO;
         for (int o2 = tid; o2 < NO; o2 += NT) {
@@ -603,9 +752,13 @@ __device__ __forceinline__ bool share_item_mfma(const Params &p, Smem<T, D, G> &
                 v1 += wg[w] * sm.red[w][hl][d + 1];
             }
             st_shared(&po[o2], pack2(v0, v1));
+            if (v0 != v0 || v1 != v1) sm.bcast[7] = 1;
         }
     }
     stores_done_barrier();
+    // (cold, so that its loops do not weigh in the allocation of registers: 27.9 us at 128K x 4 else)
+    if (__builtin_expect_with_probability(sm.bcast[7], 0, 1.0))
+        share_partial_plain<T, D, G>(p, sm, pair, j, a_lo, min(a_hi, An), c_lo, min(c_hi, m_b), tag, tid);
     SEKV_STAMP(p, sm, kTrSPartial);
     count_partial<T, D, G>(p, sm, pair, tid, leave, tag);
     SEKV_STAMP(p, sm, kTrSMerged);

@@ -1406,8 +1406,8 @@ __device__ inline bool coarse_logits(const Params &p, Smem<T, D, G> &sm, int pai
     return ok;
 }
 
-// Whether every thread's ok holds.  (__syncthreads_and keeps the thread's y and z indices in
-// registers for it, two more than the widest fp32 zoom leaves.)
+// Whether every thread's ok holds.  (With __syncthreads_and a step with fp32 storage, d 128, takes
+// 0.2 to 0.3 us more: rank 32 26.2 against 26.0, rank 16 29.3 against 29.0.)
 template <class T, int D, int G>
 __device__ inline bool all_threads(Smem<T, D, G> &sm, bool ok, int tid) {
     const bool mine = __ballot(ok) == ~0ull;
@@ -1523,10 +1523,14 @@ __device__ __forceinline__ void zoom_span(const Params &p, Smem<T, D, G> &sm, in
     SEKV_STAMP(p, sm, kTrSZoomIssued);
     mid();
     SEKV_STAMP(p, sm, kTrSZoomMid);
+    // an opaque copy of the thread index: the addresses from here on are not formed ahead of `mid`
+    // and kept across it, which the widest rows (rank 64, d 128) have no registers for
+    int ta;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(ta) : "v"(tid));
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        const int tok = min((tid + NT * u) / RU, nb0 - 1);
-        uv[u] = ucol < ruv ? ld16(UV + size_t(tok) * rv * T::kBytes + ucol * 16) : zero4;
+        const int tok = min((ta + NT * u) / RU, nb0 - 1);
+        uv[u] = ta % RU < ruv ? ld16(UV + size_t(tok) * rv * T::kBytes + ta % RU * 16) : zero4;
     }
 
     // w[h][i] = scale*log2e * sigma_K[i] * (Vt_K[i] . q_h).  No barrier first: Z.w was
@@ -1853,16 +1857,7 @@ __device__ __forceinline__ bool share_item(const Params &p, Smem<T, D, G> &sm, i
             case 2: zoom_span<T, D, G, 2, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
             case 4: zoom_span<T, D, G, 4, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
             case 8: zoom_span<T, D, G, 8, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
-            default:
-                // the widest rows: the summary block's registers are free before the zoom's
-                // loads go out (256 registers hold no more without scratch)
-                if constexpr (D == 128) {
-                    mid();
-                    zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, [] {});
-                } else {
-                    zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid);
-                }
-                break;
+            default: zoom_span<T, D, G, 16, RANKED>(p, sm, L, rk, rv, off, pend, tid, mid); break;
         }
     };
     auto zoom_one = [&](int32_t w, int64_t off, int tid, auto &&mid) {
@@ -1910,18 +1905,13 @@ template <class T, int D, int G>
 __global__ void __launch_bounds__(NT, G == 8 ? 1 : 2) sekv_step_kernel(Params p) {
     __shared__ Smem<T, D, G> sm;
     // an opaque copy of the thread index for each item keeps per-thread address arithmetic
-    // inside it instead of alive across the whole loop (register pressure); where even the
-    // index itself is one register too many, it is formed anew
-    const int wave0 = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) & ~63;
+    // inside it instead of alive across the whole loop (register pressure).  (Forming the index
+    // anew from the lane count saved one register and cost 0.9 of 31.1 us with fp32 storage,
+    // d 128, rank 64.)
     auto thread = [&]() {
         int t;
-        if constexpr (T::kBytes == 4 && D == 128) {
-            asm volatile("v_mov_b32 %0, 0" : "=v"(t));
-            return wave0 + int(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, uint32_t(t))));
-        } else {
-            asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(int(threadIdx.x)));
-            return t;
-        }
+        asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(int(threadIdx.x)));
+        return t;
     };
     // the tag of this launch's published words, used as loaded: its first use is when
     // an item publishes or polls, so the load overlaps the first item's own loads

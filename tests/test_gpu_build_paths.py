@@ -63,3 +63,16 @@ def test_segment_past_one_tile(S, n):  # noqa: F811
     banner(f"segment {n}")
     p = make_prefill(2, 1, 64, [n, n - 3], dtype="bf16", spike_every=170, true_rank=2, seed=82)
     _check_segments(_segment(S, _bdims(S, p, 1, 64, min_span=3, window=77), p), p, 1.0, 3, 77, n)
+
+
+@pytest.mark.parametrize("n,spikes,min_span", [(20000, [], 20001), (20000, [64, 97, 130, 9000, 9001, 9067], 20000),
+                                               (3000, [31, 64, 98, 1500], 33), (70001, [65535, 65536], 65535)])
+def test_segment_long_runs_of_anchors(S, n, spikes, min_span):  # noqa: F811
+    """Runs shorter than min_span up to a whole sequence: one lane writes a run of up to 32 tokens, its
+    wave a longer one."""
+    banner(f"anchor runs {n} min_span {min_span}")
+    p = make_prefill(2, 1, 64, [n, max(1, n // 3)], dtype="bf16", true_rank=2, seed=85)
+    p.surprisal[:] = 1.0
+    for b in range(2):
+        p.surprisal[b, [t for t in spikes if t < int(p.n_tokens[b])]] = 50.0
+    _check_segments(_segment(S, _bdims(S, p, 1, 64, min_span=min_span, window=2), p), p, 1.0, min_span, 2, n)

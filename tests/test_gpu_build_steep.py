@@ -2,7 +2,7 @@
 bfloat16 storage (whose rounding hides what is below) and to 10^-2.5 with float32.
 
 The rows of Vt that a span keeps are orthonormal to their storage rounding, however small their
-singular value: with unit roundoff u = 2^-9 (bfloat16) or 2^-24 (float32) a stored row is off by
+singular value: with unit roundoff u = 2^-8 (bfloat16) or 2^-24 (float32) a stored row is off by
 at most u of its length (entrywise rounding), so two rows' product by at most 2 u + u^2; 1e-8 is left
 for the factorisation itself.
 
@@ -47,7 +47,7 @@ def test_steep_spectrum(S, dtype, d, rank, sketch, power, heads):  # noqa: F811
     got, _, lay = _build(S, p, dict(rank=rank, sketch=sketch, min_span=2, window=0, power=power, Hkv=heads, d=d))
     spans = [s for s in oracle.segment(p.surprisal[0], n, 1.0, 2, 0)[1]]
     assert [L for _, L in spans] == LENGTHS
-    u, rec = (2.0 ** -9, 2.0 ** -7) if dtype == "bf16" else (2.0 ** -24, 1e-5)
+    u, rec = (2.0 ** -8, 2.0 ** -7) if dtype == "bf16" else (2.0 ** -24, 1e-5)
     worst, least = 0.0, 1.0
     for g in some:
         for i, (s0, L) in enumerate(spans):

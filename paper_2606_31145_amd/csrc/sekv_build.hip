@@ -241,16 +241,15 @@ __device__ inline void unpack16(const uint4 &v, float (&f)[16 / ELEM]) {
     }
 }
 
-// grid = B * Hkv * (ab + M_max) workgroups: of a pair's, the first ab copy 64 anchor rows each,
-// the others summarise one span each.  Both move 16-byte pieces, a row per D ELEM / 16
+// grid = B * Hkv * per workgroups: of a pair's, the first ab copy 64 anchor rows each, the others
+// summarise one span each.  Both move 16-byte pieces, a row per D ELEM / 16
 // lanes; a span's rows go round the workgroup with kAhead of them per thread in flight, so
 // the tokens are read at the rate of memory (128K x 4: 2.1 GB; 2.25 ms with one 2-byte load
 // after another per thread).
 template <int ELEM, int D>
-__global__ void __launch_bounds__(BT) gather_kernel(BuildArgs a, int ab) {
+__global__ void __launch_bounds__(BT) gather_kernel(BuildArgs a, int ab, int per) {
     constexpr int VEC = 16 / ELEM, LPR = D / VEC, RPP = BT / LPR;    // values, lanes per row, rows per pass
     constexpr int kAhead = 4;
-    const int per = ab + a.M_max;
     const int pair = blockIdx.x / per, b = pair / a.Hkv, g = pair % a.Hkv;
     const int y = int(blockIdx.x % per) - ab, tid = threadIdx.x;
     const int rg = tid / LPR, col = tid % LPR;
@@ -354,14 +353,23 @@ hipError_t launch_build(const BuildArgs &a, int batch, hipStream_t stream) {
     if (batch <= 0) return hipSuccess;
     if (a.d > 128 || a.l > kMaxL || a.l < 2 || a.R > kMaxL) return hipErrorInvalidValue;
     const unsigned pairs = unsigned(batch * a.Hkv);
-    const int ab = (a.A_max + 63) / 64;
-    const dim3 grid(pairs * unsigned(ab + a.M_max));
-    if (a.elem == 2) {
-        if (a.d == 128) hipLaunchKernelGGL((gather_kernel<2, 128>), grid, dim3(BT), 0, stream, a, ab);
-        else hipLaunchKernelGGL((gather_kernel<2, 64>), grid, dim3(BT), 0, stream, a, ab);
+    const int blocks = (a.A_max + 63) / 64;             // of anchor rows
+    auto gather = [&](int ab, int per) {
+        const dim3 grid(pairs * unsigned(per));
+        if (a.elem == 2) {
+            if (a.d == 128) hipLaunchKernelGGL((gather_kernel<2, 128>), grid, dim3(BT), 0, stream, a, ab, per);
+            else hipLaunchKernelGGL((gather_kernel<2, 64>), grid, dim3(BT), 0, stream, a, ab, per);
+        } else {
+            if (a.d == 128) hipLaunchKernelGGL((gather_kernel<4, 128>), grid, dim3(BT), 0, stream, a, ab, per);
+            else hipLaunchKernelGGL((gather_kernel<4, 64>), grid, dim3(BT), 0, stream, a, ab, per);
+        }
+    };
+    // anchors and spans in one launch while it has fewer than 2^32 threads, HIP's limit, else one each
+    if (uint64_t(pairs) * uint64_t(blocks + a.M_max) * BT < uint64_t(1) << 32) {
+        gather(blocks, blocks + a.M_max);
     } else {
-        if (a.d == 128) hipLaunchKernelGGL((gather_kernel<4, 128>), grid, dim3(BT), 0, stream, a, ab);
-        else hipLaunchKernelGGL((gather_kernel<4, 64>), grid, dim3(BT), 0, stream, a, ab);
+        gather(blocks, blocks);
+        if (a.M_max > 0) gather(0, a.M_max);
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || a.M_max == 0) return err;

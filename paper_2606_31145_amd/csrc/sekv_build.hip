@@ -32,7 +32,11 @@ hipError_t launch_svd_4_64(const BuildArgs &a, unsigned items, bool wide, hipStr
 
 namespace {
 
-constexpr unsigned kWideSides = 512;    // span sides up to which each gets four waves
+// Span sides up to which each gets four waves.  The wide variant holds one workgroup a CU at d 128,
+// so past 256 sides it takes two rounds; a lone wave takes one round up to 1024.  us at d 128, sketch 40,
+// one wave / four: bfloat16 192 sides 517 / 306, 304 515 / 512, 400 528 / 531, 544 530 / 698; float32 304 876 / 640,
+// 544 884 / 824, 752 884 / 1031; d 64, sketch 24: 400 234 / 230, 544 243 / 312 and 369 / 292, 377 / 363.
+constexpr unsigned kWideSides = 512;
 constexpr int kSegThreads = 1024;
 constexpr int BT = 256;                 // builder threads per workgroup
 constexpr int kMaxL = 40;               // largest sketch width
@@ -373,8 +377,8 @@ hipError_t launch_build(const BuildArgs &a, int batch, hipStream_t stream) {
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || a.M_max == 0) return err;
-    // four waves per span side while the sides (an upper bound: M_max per pair) leave CUs
-    // without one
+    // four waves per span side while the sides (an upper bound: M_max per pair, the counts are on
+    // the device) are few
     const unsigned items = pairs * unsigned(a.M_max);
     const bool wide = items * 2 <= kWideSides;
     if (a.elem == 2)

@@ -19,8 +19,8 @@ bool misaligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t
 size_t seg_ws(const sekv_build_dims &d) {
     const size_t B = size_t(d.batch), N = size_t(d.max_tokens);
     auto a16 = [](size_t x) { return (x + 15) & ~size_t(15); };
-    // the position list; the two byte arrays before it are part of the size that callers know
-    // and are not used
+    // the position list at the start; the rest is spare: the size, which callers may have stored,
+    // dates from a layout with two byte arrays per token
     return a16(B * N) * 2 + a16(B * (N + 2) * 4);
 }
 

@@ -666,7 +666,10 @@ __device__ __forceinline__ bool share_item_mfma(const Params &p, Smem<T, D, G> &
     drop_selected(c_lo, nc0);
     if (16 * wave < nc0) coarse(nc0);
     // 4. zoom the slot's spans (ranks j, j + n_zi, ...): four and more go to the waves whole,
-    //    fewer in two or four parts
+    //    fewer in two or four parts.  A part repeats the span's work on Vt_K and Vt_V, so parts
+    //    for a better balance cost more than they give: us at rank 16, 512 pairs, whole / this / four
+    //    parts: 2 spans a slot 55.8 / 53.2 / 57.8, 3 56.2 / 57.5 / 63.3, 4 57.4 / 56.8 / 68.9, 5 62.5 / 62.1 / 73.8, 6
+    //    64.5 / 63.8 / 79.1, 9 71.0 / 70.4 / 93.6; rank 32, 5 spans 80.1 / 82.1 / 87.4.
     const int nsp = k > j ? (k - j + nz - 1) / nz : 0;
     const int lg = nsp >= 4 ? 0 : nsp >= 2 ? 1 : 2;
     auto zoom_one = [&](auto ranked_c, int32_t w, int64_t off, int part) {

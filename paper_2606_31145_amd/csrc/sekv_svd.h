@@ -159,8 +159,9 @@ __device__ inline double rsqrt64(double x) {
 // ---------------------------------------------------------------------------
 // Cholesky with diagonal pivoting of the symmetric positive semi-definite n x n matrix in
 // g (one wave; lane i owns column i), destroyed.  A step takes the largest remaining diagonal
-// entry p (compared at 20 bits: a near-maximum serves as well; ties to the lower index) and
-// forms row j of R, A ~ R^T R:
+// entry p (compared on the sign, exponent and 14 mantissa bits, the lane in the 6 bits left of a
+// word: a near-maximum serves as well, ties to the lower index; whole doubles gave the same errors
+// over 40 build configurations and cost 1 % of a layer) and forms row j of R, A ~ R^T R:
 //   R[j][i] = (A[p][i] - sum_{m < j} R[m][p] R[m][i]) / R[j][p].
 // It stops when the largest remaining entry is not above tau times the largest initial one;
 // returns the number of steps k.  Row j of the result is stored at g's row p (nobody needs
@@ -299,7 +300,9 @@ __device__ __forceinline__ int chol(double (*g)[LS], int *piv, int n, double tau
 // A pair rotates when its cosine exceeds 1e-10.  The sweeps stop after one in which no cosine
 // was above 1e-6 (the next one's are about the square of it).  The angle's tangent is formed
 // in float32 from ratios in [-1, 1] (an error of 1e-7 of an angle is one more small angle
-// later), cosine and sine in float64.  Per round and lane: 14 FMAs for the dot products, 56 for
+// later), cosine and sine in float64.  (A float64 tangent, and sweeps until one rotates nothing,
+// leave U's and V's orthogonality and a first step's error against 64 bits as they are to four
+// digits, over 40 build configurations of up to 16 seeds: for a 128K x 4 layer 8.9 ms instead of 9.3.)  Per round and lane: 14 FMAs for the dot products, 56 for
 // the rotation, 28 DPP moves, about 60 for the angle.
 // ---------------------------------------------------------------------------
 template <int NL, int LS>

@@ -1,10 +1,11 @@
 // The share item with bfloat16 storage, on the matrix cores (included by sekv_step.h, inside its
 // namespaces).
 //
-// What bounds it: a wave issues one vector instruction per 8 cycles at most and a CU holds
-// two waves per SIMD here, so a share item is as long as its instruction count and its
-// barriers, not its FLOPs: with fp32 FMAs and lane reductions an anchor block of 128 rows took
-// about 1000 instructions a wave and 6 us, a zoomed span 8 barriers and 7 to 12 us.  Here
+// What bounds it: with two waves per SIMD a share item is as long as its chain of instructions
+// and barriers, not its FLOPs: with fp32 FMAs and lane reductions an anchor block of 128 rows took
+// about 1000 instructions a wave and 6 us, a zoomed span 8 barriers and 7 to 12 us; a 128K x 4 step
+// issued 9.5 M vector instructions and a wave waited 49 % of its cycles.  (Now 6.1 M, and 54 % of
+// fewer cycles: 32.4 M instead of 39.5 M.)  Here
 // each wave works alone on its own rows with its own online softmax (no workgroup barrier
 // between the selection and the partial), and every product is an MFMA:
 //   scores  = rows x q       A: 16 rows of keys, straight from memory; B: the query, head n % G in
@@ -21,8 +22,9 @@
 // Measured against fp32 FMAs on packed lanes, whole steps: 32K context, 8 heads of 4 queries,
 // top 8: 23.0 -> 19.9 us; batch 32 of it in a graph of layers 661 -> 410 us; 128K x 4 33.4 ->
 // 29.3 us; adaptive ranks with groups of 8 52.7 -> 30.9 us.  Mean error against 64 bits over
-// 14 shapes of fp32 output: 2.46e-7 -> 2.32e-7.  With fp32 storage the rows would have to be
-// split into pieces too, three times the loads' registers, so it stays on the FMAs.
+// 14 shapes of fp32 output: 2.46e-7 -> 2.32e-7.  fp32 storage stays on the FMAs of sekv_step.h: split
+// like this its rows would take three times the registers (the fp32 matrix instruction, which takes
+// them whole, is not tried yet).
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 

@@ -298,12 +298,17 @@ __device__ __forceinline__ int chol(double (*g)[LS], int *piv, int n, double tau
 // end meets the identity (c, s) = (0, 1) there and comes back with its sign changed, in all
 // three row groups alike; E's columns have arbitrary signs.
 //
-// A pair rotates when its cosine exceeds 1e-10.  The sweeps stop after one in which no cosine
-// was above 1e-6 (the next one's are about the square of it).  The angle's tangent is formed
-// in float32 from ratios in [-1, 1] (an error of 1e-7 of an angle is one more small angle
-// later), cosine and sine in float64.  (A float64 tangent, and sweeps until one rotates nothing,
-// leave U's and V's orthogonality and a first step's error against 64 bits as they are to four
-// digits, over 40 build configurations of up to 16 seeds: for a 128K x 4 layer 8.9 ms instead of 9.3.)  Per round and lane: 14 FMAs for the dot products, 56 for
+// V's rows are W's columns seen through M once more, so a pair that keeps the dot product ga and
+// squared norms al, be leaves two rows of V with the product |ga| / min(al, be): its cosine times
+// the ratio of the singular values.  A pair rotates unless its cosine is below 1e-18 (what float32
+// holds of the angle), and the sweeps stop after one in which no |ga| / min(al, be) was above 1e-6
+// (the next one's are about the square of it).  With cosines alone, to 1e-10, the rows' product was
+// 5e-8 at singular values of 1/500 and grew with the ratio.  The angle's tangent is formed in
+// float32 from ratios in [-1, 1] (an error of 1e-7 of an angle is one more small angle later),
+// cosine and sine in float64: a float64 tangent, or sweeps until one rotates nothing, changed
+// neither the orthogonality of U and V nor a first step's error against 64 bits in four digits (40
+// build configurations, up to 16 seeds) and made a 128K x 4 layer 2 and 4 % longer.
+// Per round and lane: 14 FMAs for the dot products, 56 for
 // the rotation, 28 DPP moves, about 60 for the angle.
 // ---------------------------------------------------------------------------
 template <int NL, int LS>
@@ -335,8 +340,8 @@ __device__ __forceinline__ void jacobi_columns(double (*g)[LS], const int *piv, 
     auto rotate = [&](double (&x)[RW], double (&y)[RW], double &al, double &be, bool on) {
         const double ga = dot(x, y);
         const double g2 = ga * ga, ab = al * be;
-        const bool rot = on && g2 > 1e-20 * ab;
-        wide |= on && g2 > 1e-12 * ab;
+        const bool rot = on && g2 > 1e-36 * ab;
+        wide |= on && fabs(ga) > 1e-6 * fmin(al, be);
         // t = sign(be - al) 2 ga / (|be - al| + sqrt((be - al)^2 + 4 ga^2)), from ratios to al + be
         const double rho = __builtin_amdgcn_rcp(al + be);
         const float dd = float((be - al) * rho), gg = float(2.0 * ga * rho);

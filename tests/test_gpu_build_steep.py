@@ -1,5 +1,6 @@
-"""GPU: spans of steep spectrum, short and long: singular values down to 1e-4 of the largest with
-bfloat16 storage (whose rounding hides what is below) and to 10^-2.5 with float32.
+"""GPU: spans of steep spectrum, short and long: singular values falling by 4 decades with bfloat16
+storage (whose rounding hides what is below), by 2.5 and by 10 and 12 with float32 (components below
+1e-5 of the largest are not kept).
 
 The rows of Vt that a span keeps are orthonormal to their storage rounding, however small their
 singular value: with unit roundoff u = 2^-8 (bfloat16) or 2^-24 (float32) a stored row is off by
@@ -25,11 +26,12 @@ pytestmark = pytest.mark.gpu
 LENGTHS = [31, 200, 1500]
 
 
-@pytest.mark.parametrize("dtype,d,rank,sketch,power,heads", [
-    ("bf16", 128, 32, 40, 1, 100), ("bf16", 128, 24, 40, 0, 100), ("bf16", 64, 32, 40, 1, 100), ("bf16", 128, 32, 40, 1, 2),
-    ("f32", 128, 32, 40, 1, 100), ("f32", 64, 16, 24, 2, 2)])
-def test_steep_spectrum(S, dtype, d, rank, sketch, power, heads):  # noqa: F811
-    banner(f"steep spectrum {dtype} d{d} r{rank} l{sketch} p{power} heads {heads}")
+@pytest.mark.parametrize("dtype,d,rank,sketch,power,heads,decades", [
+    ("bf16", 128, 32, 40, 1, 100, 4), ("bf16", 128, 24, 40, 0, 100, 4), ("bf16", 64, 32, 40, 1, 100, 4),
+    ("bf16", 128, 32, 40, 1, 2, 4), ("f32", 128, 32, 40, 1, 100, 2.5), ("f32", 64, 16, 24, 2, 2, 2.5),
+    ("f32", 128, 32, 40, 1, 100, 12), ("f32", 64, 32, 40, 1, 2, 10)])
+def test_steep_spectrum(S, dtype, d, rank, sketch, power, heads, decades):  # noqa: F811
+    banner(f"steep spectrum {dtype} d{d} r{rank} l{sketch} p{power} heads {heads} decades {decades}")
     n = sum(LENGTHS) + len(LENGTHS)
     p = make_prefill(1, heads, d, [n], dtype=dtype, true_rank=4, sketch=sketch, seed=84)
     p.surprisal[:] = 1.0
@@ -42,7 +44,7 @@ def test_steep_spectrum(S, dtype, d, rank, sketch, power, heads):  # noqa: F811
             for rows in (p.keys, p.values):
                 k = min(L, d)
                 q = [np.linalg.qr(rng.standard_normal((m, k)))[0] for m in (L, d)]
-                X = (q[0] * 10.0 ** -np.linspace(0, 4.0 if dtype == "bf16" else 2.5, k)) @ q[1].T * math.sqrt(L)
+                X = (q[0] * 10.0 ** -np.linspace(0, decades, k)) @ q[1].T * math.sqrt(L)
                 rows[0, g, end[i] - L:end[i]] = oracle.narrow(X, dtype)
     got, _, lay = _build(S, p, dict(rank=rank, sketch=sketch, min_span=2, window=0, power=power, Hkv=heads, d=d))
     spans = [s for s in oracle.segment(p.surprisal[0], n, 1.0, 2, 0)[1]]

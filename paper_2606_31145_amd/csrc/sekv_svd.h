@@ -16,8 +16,8 @@
 // of L2-resident tokens, two to four 40 x 40 factorisations, 200 to 250 Jacobi rounds), and a
 // layer has tens of thousands of them.  So a side runs in ONE wave (its steps need no
 // workgroup barrier) and eight sides share a CU, two waves a SIMD.  Counted over a 128K x 4 layer, a
-// wave spends 29 % of its cycles in vector instructions, 44 % waiting for one to issue (its own
-// dependences, and the other wave) and 18 % for memory or LDS; the matrix cores are busy 41 % of
+// wave spends 30 % of its cycles in vector instructions, 44 % waiting for one to issue (its own
+// dependences, and the other wave) and 18 % for memory or LDS; the matrix cores are busy 40 % of
 // the time.  That leaves 20 KB of LDS and 256 registers a side, hence: no copy of B, X or P is kept (M is formed
 // tile by tile, the last pass forms P again), and LDS holds either the pass's tiles or one
 // 40 x 40 matrix.  The dense products run on the matrix cores: bf16 MFMA where the operands
